@@ -75,10 +75,10 @@ int encode_table(const dsk_job *jobs, int n, const dsk_tune &t, JobDev *out, Sub
         for (int i = 0; i < n; ++i) {
             const dsk_job &j = jobs[i];
             if ((j.vol != nullptr) != vol) continue;
-            const bool vec = vec_ok(t, j.dims, j.out_width, j.in, 0, j.vol,
-                                    (int64_t)j.dims.rows * j.dims.cols);
+            const int vec = vec_mode(t, j.dims, j.out_width, j.in, 0, j.vol,
+                                     (int64_t)j.dims.rows * j.dims.cols);
             const int64_t tx = tiles_x(j.out_width, t, vec);
-            const int64_t eb = edge_blocks(j.dims, j.out_width, t, vec, j.vol != nullptr);
+            const int64_t eb = edge_blocks(j.dims, j.out_width, t, vec);
             if (tx > kMaxI32) return -1;
             JobDev r;
             r.in = j.in;
@@ -94,7 +94,7 @@ int encode_table(const dsk_job *jobs, int n, const dsk_tune &t, JobDev *out, Sub
             r.R = j.dims.rows;
             r.C = j.dims.cols;
             r.tiles_x = (int32_t)tx;
-            r.vec = vec ? 1 : 0;
+            r.vec = vec;
             r.edge_blocks = (int32_t)eb;
             r.tau256 = 0;
             out[k++] = r;
@@ -248,7 +248,10 @@ int time_shape(dsk_batch *bt, const dsk_tune &t, hipStream_t s, int reps, double
 int launch_per_job(const dsk_batch *bt, bool tuned, hipStream_t s) {
     for (size_t i = 0; i < bt->jobs.size(); ++i) {
         const dsk_job &j = bt->jobs[i];
-        const dsk_tune &t = tuned ? bt->job_tunes[i] : default_tune(j.vol);
+        const dsk_tune t = tuned ? bt->job_tunes[i]
+                                 : default_tune(j.in, 0, j.dims,
+                                                (int64_t)j.dims.rows * j.dims.cols, j.vol,
+                                                j.out_width);
         const int st = launch_forward(j.in, 0, j.dims, j.offsets_dev, j.shift_px, j.origin, j.vol,
                                       j.psum, j.pmax, j.out_width, t, s);
         if (st != DSK_OK) return st;

@@ -7,12 +7,14 @@
 #include <type_traits>
 
 #include "deskew.h"
+#include "kernels.hpp"
 
 namespace dsk {
 
 constexpr int64_t kMaxI32 = 2147483647;
 
-// Default forward launch shape: 64-thread workgroups, one 4-column group per
+// Default forward launch shape (default_tune adapts its pace and pipeline to
+// the frame): 64-thread workgroups, one 4-column group per
 // lane, non-temporal stores, 2-plane pipeline (built for 8 waves per SIMD),
 // paced at 5700 GB/s.  On the 512x512x2048 stack, back to back, the launch
 // time follows the pace (bytes / pace + about 3 us) up to the cliff:
@@ -37,10 +39,6 @@ constexpr dsk_tune kDefaultTune = {64, 4, 1, 2, 0, 5700};
 // began before they did (1-3% slower when they were).
 constexpr dsk_tune kDefaultProjTune = {64, 4, 1, 4, 0, 9000};
 
-inline const dsk_tune &default_tune(const void *vol) {
-    return vol ? kDefaultTune : kDefaultProjTune;
-}
-
 inline bool dims_ok(dsk_dims d) {
     return d.planes > 0 && d.rows > 0 && d.cols > 0;
 }
@@ -57,25 +55,36 @@ inline bool tune_ok(const dsk_tune &t) {
 // Compute units of the current device (cached per device).
 int device_cus();
 
-// The aligned vector kernel applies when every row's flat volume and stack
-// offsets keep one residue mod 4 across planes and the buffers are aligned.
-inline bool vec_ok(const dsk_tune &t, dsk_dims d, int64_t width, const void *in, int in_is_f32,
-                   const float *vol, int64_t in_plane) {
-    if (t.per_thread < 4) return false;
-    if ((int64_t)d.planes * d.rows * d.cols < 64 || in_plane < 8) return false;
-    if (width >= (int64_t(1) << 27) || d.cols >= (1 << 27)) return false;
-    if (((int64_t)d.rows * width) % 4 != 0 || in_plane % 4 != 0) return false;
-    const uintptr_t ia = in_is_f32 ? 15 : 7;
-    if ((uintptr_t)in & ia) return false;
-    if (vol && ((uintptr_t)vol & 15)) return false;
-    return true;
+// Which kernel tiles a frame.  The aligned vector kernel applies when every
+// row's flat volume and stack offsets keep one residue mod 4 across planes
+// and the buffers are aligned (and, without a volume, when no columns are
+// left over); the general vector kernel takes every other frame at least one
+// group wide; the scalar kernel the rest, and shapes of fewer than 4 columns
+// per thread.  Measured with a volume on 201x487x1531 uint16 (45 deg, odd in
+// every side, 1.06 GB): scalar 0.641 ms, general 0.211 ms; projections only
+// 0.283 -> 0.086 ms.  Aligned frames keep the aligned kernel with a volume:
+// its tiles can start on 128-byte boundaries, which holds a faster pace
+// (default_tune).
+inline int vec_mode(const dsk_tune &t, dsk_dims d, int64_t width, const void *in, int in_is_f32,
+                    const float *vol, int64_t in_plane) {
+    if (t.per_thread < 4) return VEC_NONE;
+    if ((int64_t)d.planes * d.rows * d.cols < 64 || in_plane < 8) return VEC_NONE;
+    if (width >= (int64_t(1) << 27) || d.cols >= (1 << 27)) return VEC_NONE;
+    const uintptr_t ia = in_is_f32 ? 15 : 7, im = in_is_f32 ? 3 : 1;
+    if (((int64_t)d.rows * width) % 4 == 0 && in_plane % 4 == 0 && ((uintptr_t)in & ia) == 0 &&
+        (vol ? ((uintptr_t)vol & 15) == 0 : width % 4 == 0))
+        return VEC_ALIGNED;
+    return width >= 4 && ((uintptr_t)in & im) == 0 && ((uintptr_t)vol & 3) == 0 ? VEC_GENERAL
+                                                                                : VEC_NONE;
 }
 
-// Column tiles of one output row.  The vector kernel tiles the row's whole
-// 4-aligned groups (at most W/4 of them); the scalar kernel tiles columns.
-inline int64_t tiles_x(int64_t width, const dsk_tune &t, bool vec) {
+// Column tiles of one output row.  The aligned vector kernel tiles the row's
+// whole 4-aligned groups (at most W/4 of them), the general one its columns
+// in groups of 4 (the last moved back to end at the row's end); the scalar
+// kernel tiles columns.
+inline int64_t tiles_x(int64_t width, const dsk_tune &t, int vec) {
     const int64_t tile = (int64_t)t.block * t.per_thread;
-    if (vec) {
+    if (vec == VEC_ALIGNED) {
         const int64_t groups = width / 4, per = tile / 4;
         const int64_t n = (groups + per - 1) / per;
         return n > 0 ? n : 1;
@@ -83,15 +92,12 @@ inline int64_t tiles_x(int64_t width, const dsk_tune &t, bool vec) {
     return (width + tile - 1) / tile;
 }
 
-// Workgroups of the vector kernel for the rows' unaligned edge columns
-// (none when the width is a multiple of 4), which it runs first: with a
-// volume one lane per (row, slot of 6), without one a wavefront per (row,
-// slot), block / 64 wavefronts per workgroup.  The kernel receives the
-// count.
-inline int64_t edge_blocks(dsk_dims d, int64_t width, const dsk_tune &t, bool vec, bool vol) {
-    if (!vec || width % 4 == 0) return 0;
-    const int64_t per = vol ? t.block : t.block / 64;
-    return (6 * (int64_t)d.rows + per - 1) / per;
+// Workgroups of the aligned vector kernel for the rows' unaligned edge
+// columns (none when the width is a multiple of 4), which it runs first: one
+// lane per (row, slot of 6).  The kernel receives the count.
+inline int64_t edge_blocks(dsk_dims d, int64_t width, const dsk_tune &t, int vec) {
+    if (vec != VEC_ALIGNED || width % 4 == 0) return 0;
+    return (6 * (int64_t)d.rows + t.block - 1) / t.block;
 }
 
 template <int V>
@@ -150,6 +156,10 @@ inline InLayout dense_layout(dsk_dims d) {
 // Bounds-violation count of the batch kernels' translation unit (batch.hip).
 int batch_bounds_violations(unsigned long long *count, bool reset);
 #endif
+
+// The launch shape of a frame when the caller gives none (deskew.hip).
+dsk_tune default_tune(const void *in, int in_is_f32, dsk_dims d, int64_t in_plane,
+                      const float *vol, int64_t width);
 
 // Launchers (deskew.hip) used by the other translation units.
 int launch_forward(const void *in, int in_is_f32, dsk_dims d, const double *offs,

@@ -96,13 +96,13 @@ int device_cus() {
 
 // Workgroups of the vector kernel one compute unit holds at once (cached
 // per kernel instance).
-template <typename TIn, int B, int G, int U, bool NT, bool VOL>
+template <typename TIn, int B, int G, int U, bool NT, bool VOL, bool GEN>
 static int vec_resident_per_cu() {
     static int occ = 0;
     if (occ <= 0) {
         int o = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, k_forward_vec<TIn, B, G, U, NT, VOL>, B,
-                                                         0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, k_forward_vec<TIn, B, G, U, NT, VOL, GEN>,
+                                                         B, 0) != hipSuccess ||
             o <= 0)
             o = 1;
         occ = o;
@@ -110,73 +110,81 @@ static int vec_resident_per_cu() {
     return occ;
 }
 
+template <typename TIn, int B, int PT, int U, bool NT, bool GEN>
+static hipError_t fwd_launch_vec(FwdArgs<TIn> a, int64_t tiles, int64_t edge, int pace_gbs,
+                                 hipStream_t s) {
+    const dim3 block(B);
+    // launches without a volume only read: no store kind to choose
+    auto kern = a.vol ? k_forward_vec<TIn, B, PT / 4, U, NT, true, GEN>
+                      : k_forward_vec<TIn, B, PT / 4, U, false, false, GEN>;
+    // Pacing holds every wavefront to one plane schedule: with a
+    // volume it keeps the write stream local; without one, wavefronts
+    // whose plane ranges start late wait for their turn.
+    int64_t cap = 0;
+    if (pace_gbs > 0)
+        cap = (int64_t)(a.vol ? vec_resident_per_cu<TIn, B, PT / 4, U, NT, true, GEN>()
+                              : vec_resident_per_cu<TIn, B, PT / 4, U, false, false, GEN>()) *
+              device_cus();
+    // without a volume a frame whose tiles do not all fit at once is
+    // not paced: its later tiles would wait out a schedule that began
+    // before they started
+    if (!a.vol && pace_gbs > 0 && tiles * a.R > cap) pace_gbs = 0;
+    auto launch_rows = [&](FwdArgs<TIn> f, int64_t f_edge) {
+        if (pace_gbs > 0) {
+            // one tile's share of a plane's bytes, timed at pace_gbs
+            // (the edge columns' workgroups are not paced)
+            const double plane_bytes = (double)f.R * f.C * sizeof(TIn) +
+                                       (f.vol ? 4.0 * (double)f.R * (double)f.W : 0.0);
+            const double t = plane_bytes / (double)(tiles * f.R) /
+                             ((double)pace_gbs * 1e9) * 1e8 * 65536.0;
+            f.tau_wg = t >= 4.0e9 ? 4000000000u : (uint32_t)t;
+            f.pace_cap = (int32_t)(cap < 1 ? 1 : (cap > kMaxI32 ? kMaxI32 : cap));
+        }
+        f.edge_wg = (int32_t)f_edge;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * f.R + f_edge)), block, 0, s, f,
+                           (int)tiles);
+        return hipGetLastError();
+    };
+    // A paced frame with a volume and more tiles than resident
+    // workgroups goes out as bands of rows that each fit, one launch
+    // after another: a second round of tiles starting as the first
+    // ones end would fall behind their schedule and spread the write
+    // stream over the volume.  Bands start at multiples of 4 rows, so
+    // every row keeps its residues mod 4 (r W and r in_row) and with
+    // them the kernel's alignment.
+    const int64_t band = cap / tiles / 4 * 4;
+    if (a.vol && pace_gbs > 0 && tiles * a.R > cap && band >= 4) {
+        const int64_t nb = (a.R + band - 1) / band;
+        const int64_t rows = ((a.R + nb - 1) / nb + 3) / 4 * 4;
+        const int64_t per = B;   // edge lanes per workgroup with a volume
+        for (int64_t r0 = 0; r0 < a.R; r0 += rows) {
+            FwdArgs<TIn> f = a;
+            const int64_t nr = a.R - r0 < rows ? a.R - r0 : rows;
+            const int64_t in_off = r0 * a.in_row;
+            f.in = a.in + in_off;
+            f.in_lo = a.in_lo + in_off;
+            f.in_hi = a.in_hi - in_off;
+            f.R = (int32_t)nr;
+            f.vol = a.vol + r0 * a.W;
+            f.psum = a.psum ? a.psum + r0 * a.W : nullptr;
+            f.pmax = a.pmax ? a.pmax + r0 * a.W : nullptr;
+            const hipError_t e = launch_rows(f, edge > 0 ? (6 * nr + per - 1) / per : 0);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+    return launch_rows(a, edge);
+}
+
 template <typename TIn, int B, int PT, int U, bool NT>
-static hipError_t fwd_launch(FwdArgs<TIn> a, bool vec, int64_t tiles, int64_t edge, int pace_gbs,
-                             hipStream_t s) {
+static hipError_t fwd_launch(const FwdArgs<TIn> &a, int vec, int64_t tiles, int64_t edge,
+                             int pace_gbs, hipStream_t s) {
     const dim3 block(B);
     if constexpr (PT >= 4) {
-        if (vec) {
-            // launches without a volume only read: no store kind to choose
-            auto kern = a.vol ? k_forward_vec<TIn, B, PT / 4, U, NT, true>
-                              : k_forward_vec<TIn, B, PT / 4, U, false, false>;
-            // Pacing holds every wavefront to one plane schedule: with a
-            // volume it keeps the write stream local; without one, wavefronts
-            // whose plane ranges start late wait for their turn.
-            int64_t cap = 0;
-            if (pace_gbs > 0)
-                cap = (int64_t)(a.vol ? vec_resident_per_cu<TIn, B, PT / 4, U, NT, true>()
-                                      : vec_resident_per_cu<TIn, B, PT / 4, U, false, false>()) *
-                      device_cus();
-            // without a volume a frame whose tiles do not all fit at once is
-            // not paced: its later tiles would wait out a schedule that began
-            // before they started
-            if (!a.vol && pace_gbs > 0 && tiles * a.R > cap) pace_gbs = 0;
-            auto launch_rows = [&](FwdArgs<TIn> f, int64_t f_edge) {
-                if (pace_gbs > 0) {
-                    // one tile's share of a plane's bytes, timed at pace_gbs
-                    // (the edge columns' workgroups are not paced)
-                    const double plane_bytes = (double)f.R * f.C * sizeof(TIn) +
-                                               (f.vol ? 4.0 * (double)f.R * (double)f.W : 0.0);
-                    const double t = plane_bytes / (double)(tiles * f.R) /
-                                     ((double)pace_gbs * 1e9) * 1e8 * 65536.0;
-                    f.tau_wg = t >= 4.0e9 ? 4000000000u : (uint32_t)t;
-                    f.pace_cap = (int32_t)(cap < 1 ? 1 : (cap > kMaxI32 ? kMaxI32 : cap));
-                }
-                f.edge_wg = (int32_t)f_edge;
-                hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * f.R + f_edge)), block, 0, s, f,
-                                   (int)tiles);
-                return hipGetLastError();
-            };
-            // A paced frame with a volume and more tiles than resident
-            // workgroups goes out as bands of rows that each fit, one launch
-            // after another: a second round of tiles starting as the first
-            // ones end would fall behind their schedule and spread the write
-            // stream over the volume.  Bands start at multiples of 4 rows, so
-            // every row keeps its residues mod 4 (r W and r in_row) and with
-            // them the kernel's alignment.
-            const int64_t band = cap / tiles / 4 * 4;
-            if (a.vol && pace_gbs > 0 && tiles * a.R > cap && band >= 4) {
-                const int64_t nb = (a.R + band - 1) / band;
-                const int64_t rows = ((a.R + nb - 1) / nb + 3) / 4 * 4;
-                const int64_t per = B;   // edge lanes per workgroup with a volume
-                for (int64_t r0 = 0; r0 < a.R; r0 += rows) {
-                    FwdArgs<TIn> f = a;
-                    const int64_t nr = a.R - r0 < rows ? a.R - r0 : rows;
-                    const int64_t in_off = r0 * a.in_row;
-                    f.in = a.in + in_off;
-                    f.in_lo = a.in_lo + in_off;
-                    f.in_hi = a.in_hi - in_off;
-                    f.R = (int32_t)nr;
-                    f.vol = a.vol + r0 * a.W;
-                    f.psum = a.psum ? a.psum + r0 * a.W : nullptr;
-                    f.pmax = a.pmax ? a.pmax + r0 * a.W : nullptr;
-                    const hipError_t e = launch_rows(f, edge > 0 ? (6 * nr + per - 1) / per : 0);
-                    if (e != hipSuccess) return e;
-                }
-                return hipSuccess;
-            }
-            return launch_rows(a, edge);
-        }
+        if (vec == VEC_ALIGNED)
+            return fwd_launch_vec<TIn, B, PT, U, NT, false>(a, tiles, edge, pace_gbs, s);
+        if (vec == VEC_GENERAL)
+            return fwd_launch_vec<TIn, B, PT, U, NT, true>(a, tiles, edge, pace_gbs, s);
     }
     hipLaunchKernelGGL((k_forward_scalar<TIn, B, PT, NT>), dim3((unsigned)(tiles * a.R)), block,
                        0, s, a, (int)tiles);
@@ -184,7 +192,7 @@ static hipError_t fwd_launch(FwdArgs<TIn> a, bool vec, int64_t tiles, int64_t ed
 }
 
 template <typename TIn>
-static hipError_t fwd_dispatch(const FwdArgs<TIn> &a, const dsk_tune &t, bool vec, int64_t tiles,
+static hipError_t fwd_dispatch(const FwdArgs<TIn> &a, const dsk_tune &t, int vec, int64_t tiles,
                                int64_t edge, hipStream_t stream) {
     return dispatch_tune(t, [&](auto B, auto P, auto U, auto NT) {
         return fwd_launch<TIn, decltype(B)::value, decltype(P)::value, decltype(U)::value,
@@ -213,6 +221,58 @@ static int64_t aligned_tiles(const float *vol, int64_t rows, int64_t width, int6
     return need;
 }
 
+// Whether a frame's tiles start on 128-byte boundaries of the volume: the
+// plane pitch keeps them there in every plane and the shifted grids need no
+// more tiles.
+static bool tiles_aligned(const float *vol, dsk_dims d, int64_t width, const dsk_tune &t, int vec) {
+    return vec == VEC_ALIGNED && vol && ((int64_t)d.rows * width) % 32 == 0 &&
+           aligned_tiles(vol, d.rows, width, (int64_t)t.block * t.per_thread / 4) <=
+               tiles_x(width, t, vec);
+}
+
+// kDefaultTune (or kDefaultProjTune without a volume) with the pace and the
+// pipeline depth that hold for the frame.  GB/s measured over frames of
+// 100-1304 rows, 256-2048 columns and 16-400 planes:
+//  * tiles on 128-byte boundaries hold 5700 (5443-5582); other tile grids
+//    leave partial lines at both ends of every store run and their cliff
+//    lies between 5200 and 5400: 201x487x1531 uint16 4022 paced 5700, 5050
+//    at 5200; float32 256x512x1024 into 1793 columns 4160 at 5700, 5110 at
+//    5100.  5100 keeps 100 of margin;
+//  * up to kSmallBytes moved and kSmallPlanes planes the last-level cache
+//    absorbs most of the writes and the wavefronts cannot drift far apart,
+//    so a launch does better unpaced: 64x512x2048 uint16 (435 MB) 6496
+//    against 5409, 48x512x2048 float32 (425 MB) 6437 against 5476.  Unaligned
+//    16-bit frames of that size do better paced at 5700 (80x511x1023: 5286
+//    against 4971), and more planes need the pacing (256x256x512, 392 MB:
+//    4441 against 3809);
+//  * with few wavefronts a compute unit a 4-plane pipeline keeps enough
+//    loads in flight: 256x256x512 (5 wavefronts) 4409 -> 5140, 256x128x1024
+//    (3.5) 3369 -> 4426; from 7 on the two are equal, from 14 on 2 planes
+//    do better.
+constexpr int kPartialLinePace = 5100;
+constexpr int64_t kSmallBytes = 450000000;
+constexpr int32_t kSmallPlanes = 100;
+constexpr int64_t kFewTilesPerCU = 6;
+
+dsk_tune default_tune(const void *in, int in_is_f32, dsk_dims d, int64_t in_plane,
+                      const float *vol, int64_t width) {
+    if (!vol) return kDefaultProjTune;
+    dsk_tune t = kDefaultTune;
+    if (!in || !dims_ok(d) || check_frame(d, 0, width) != DSK_OK) return t;   // refused later
+    const int vec = vec_mode(t, d, width, in, in_is_f32, vol, in_plane);
+    if (vec == VEC_NONE) return t;
+    const int64_t bytes =
+        (int64_t)d.planes * d.rows * ((in_is_f32 ? 4 : 2) * (int64_t)d.cols + 4 * width);
+    const bool aligned = tiles_aligned(vol, d, width, t, vec);
+    if (bytes <= kSmallBytes && d.planes <= kSmallPlanes) {
+        if (aligned || in_is_f32) t.pace_gbs = 0;
+    } else if (!aligned) {
+        t.pace_gbs = kPartialLinePace;
+    }
+    if (tiles_x(width, t, vec) * d.rows <= kFewTilesPerCU * device_cus()) t.unroll = 4;
+    return t;
+}
+
 int launch_forward_layout(const void *in, int in_is_f32, dsk_dims d, const InLayout &lay,
                           const double *offs, double shift, int64_t origin, float *vol,
                           float *psum, float *pmax, int64_t width, const dsk_tune &t,
@@ -227,15 +287,10 @@ int launch_forward_layout(const void *in, int in_is_f32, dsk_dims d, const InLay
     if (lay.row < d.cols || lay.plane < (int64_t)(d.rows - 1) * lay.row + d.cols || lay.lo < 0 ||
         lay.hi < last + d.cols)
         return DSK_ESHAPE;
-    const bool vec = vec_ok(t, d, width, in, in_is_f32, vol, lay.plane);
-    // volume rows' tiles on 128-byte boundaries when the plane pitch keeps
-    // them there in every plane and the shifted grids need no more tiles
-    const int64_t tiles_plain = tiles_x(width, t, vec);
-    const bool align = vec && vol && ((int64_t)d.rows * width) % 32 == 0 &&
-                       aligned_tiles(vol, d.rows, width, (int64_t)t.block * t.per_thread / 4) <=
-                           tiles_plain;
-    const int64_t tiles = tiles_plain;
-    const int64_t edge = edge_blocks(d, width, t, vec, vol != nullptr);
+    const int vec = vec_mode(t, d, width, in, in_is_f32, vol, lay.plane);
+    const bool align = tiles_aligned(vol, d, width, t, vec);
+    const int64_t tiles = tiles_x(width, t, vec);
+    const int64_t edge = edge_blocks(d, width, t, vec);
     if (tiles * (int64_t)d.rows + edge > kMaxI32) return DSK_ESHAPE;
     hipError_t e;
     if (in_is_f32) {
@@ -273,7 +328,8 @@ extern "C" int dsk_deskew_u16(const uint16_t *in, dsk_dims d, dsk_geom g, float 
     st = dsk_plan(d, nullptr, s, &w, &b);
     if (st != DSK_OK) return st;
     if (out_width > 0) w = out_width;
-    return launch_forward(in, 0, d, nullptr, s, b, vol, psum, pmax, w, default_tune(vol), stream);
+    return launch_forward(in, 0, d, nullptr, s, b, vol, psum, pmax, w,
+                          default_tune(in, 0, d, (int64_t)d.rows * d.cols, vol, w), stream);
 }
 
 extern "C" int dsk_deskew_channel_u16(const uint16_t *frames, int64_t frame_cols, int64_t col0,
@@ -292,7 +348,7 @@ extern "C" int dsk_deskew_channel_u16(const uint16_t *frames, int64_t frame_cols
     const int64_t plane = (int64_t)d.rows * frame_cols;
     const InLayout lay{frame_cols, plane, col0, (int64_t)d.planes * plane - col0};
     return launch_forward_layout(frames + col0, 0, d, lay, nullptr, s, b, vol, psum, pmax, w,
-                                 default_tune(vol), stream);
+                                 default_tune(frames + col0, 0, d, plane, vol, w), stream);
 }
 
 extern "C" int dsk_deskew_offsets_u16(const uint16_t *in, dsk_dims d, const double *offsets_dev,
@@ -300,7 +356,8 @@ extern "C" int dsk_deskew_offsets_u16(const uint16_t *in, dsk_dims d, const doub
                                       int64_t out_width, hipStream_t stream) {
     if (!offsets_dev || out_width <= 0) return DSK_EINVAL;
     return launch_forward(in, 0, d, offsets_dev, 0.0, origin, vol, psum, pmax, out_width,
-                          default_tune(vol), stream);
+                          default_tune(in, 0, d, (int64_t)d.rows * d.cols, vol, out_width),
+                          stream);
 }
 
 extern "C" int dsk_deskew_offsets_f32(const float *in, dsk_dims d, const double *offsets_dev,
@@ -308,7 +365,8 @@ extern "C" int dsk_deskew_offsets_f32(const float *in, dsk_dims d, const double 
                                       int64_t out_width, hipStream_t stream) {
     if (!offsets_dev || out_width <= 0) return DSK_EINVAL;
     return launch_forward(in, 1, d, offsets_dev, 0.0, origin, vol, psum, pmax, out_width,
-                          default_tune(vol), stream);
+                          default_tune(in, 1, d, (int64_t)d.rows * d.cols, vol, out_width),
+                          stream);
 }
 
 extern "C" int dsk_deskew_offsets_tuned(const void *in, int in_is_f32, dsk_dims d,
@@ -317,7 +375,9 @@ extern "C" int dsk_deskew_offsets_tuned(const void *in, int in_is_f32, dsk_dims 
                                         int64_t out_width, const dsk_tune *tune,
                                         hipStream_t stream) {
     if (out_width <= 0) return DSK_EINVAL;
-    const dsk_tune t = tune ? *tune : default_tune(vol);
+    const dsk_tune t = tune ? *tune
+                            : default_tune(in, in_is_f32, d, (int64_t)d.rows * d.cols, vol,
+                                           out_width);
     return launch_forward(in, in_is_f32 ? 1 : 0, d, offsets_dev, shift_px, origin, vol, psum,
                           pmax, out_width, t, stream);
 }

@@ -18,7 +18,14 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace dsk {
+
+// How a frame is tiled (vec_mode in common.hpp): by the scalar kernel, by the
+// vector kernel on 16-byte aligned groups, or by the vector kernel's general
+// form.
+enum { VEC_NONE = 0, VEC_ALIGNED = 1, VEC_GENERAL = 2 };
 
 // Per-plane interpolation coefficients, computed in FP64 from the offset
 // exactly as the host plan does (no contraction: explicit round-to-nearest
@@ -272,13 +279,15 @@ __device__ __forceinline__ void fwd_tile_scalar(const FwdArgs<TIn> &a, int r, in
 // that is the same for the whole wavefront), or 16 + 4 bytes of float.
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// the same 16 bytes at any 4-byte boundary (one instruction on gfx950)
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
-template <bool NT>
+template <bool NT, typename V = f32x4>
 __device__ __forceinline__ void store_f32x4(float *p, f32x4 v) {
     if constexpr (NT)
-        __builtin_nontemporal_store(v, (f32x4 *)p);
+        __builtin_nontemporal_store((V)v, (V *)p);
     else
-        *(f32x4 *)p = v;
+        *(V *)p = v;
 }
 
 // Raw source window of one 4-column group.  uint16: the 6 pixels (12 bytes)
@@ -403,7 +412,15 @@ __device__ __forceinline__ int edge_col(const RowGeo &g, int W, int j) {
 //
 // Every path does the same per-voxel arithmetic and adds planes to the FP64
 // sum in plane order, so no class or pass split changes a bit of the result.
-template <typename TIn, int BLOCK, int G, int UNR, bool NT, bool VOL>
+//
+// GEN: frames whose planes, rows or buffers keep no common 16-byte phase.
+// Groups start at column 0 of every row and the row's last group is moved
+// back to end at column W - 1 (it repeats up to 3 columns of the group
+// before it: identical values to identical addresses), so there are no edge
+// columns; volume stores are 16 bytes at any 4-byte boundary; and a 16-bit
+// window's parity is a plane's (an odd plane pitch) and a lane's own (the
+// moved group) instead of the launch's.
+template <typename TIn, int BLOCK, int G, int UNR, bool NT, bool VOL, bool GEN>
 struct VecTile {
     enum { OUT = 0, IN = 1, MIXED = 2 };
     using Win = RawWin<TIn>;
@@ -417,7 +434,8 @@ struct VecTile {
     int64_t rstep, ostep;
     const TIn *rp0;                    // row r of plane 0
     float *op0;                        // volume row r of plane 0 (or null)
-    int gi[G], gfirst[G], glast[G];
+    // columns from ca: the lane's group, the wavefront's first and last
+    int gx[G], pfirst[G], plast[G];
     bool alive;
     uint64_t t0;                       // pacing origin (this wavefront's start)
     uint32_t tau;                      // pacing period per plane, 1/256 ticks (0 = none)
@@ -426,12 +444,13 @@ struct VecTile {
     float mx[G][4];
     // chunk lane data (plane c0 + lane): first needed pixel of group 0 (s0),
     // window start and shift packed as (s0 - sh) * 2 + sh, and the weights
+    // (GEN: s0 * 2 + the parity of the plane's row start)
     int ls0, lwin;
     float lwlo, lwhi;
 
     __device__ __forceinline__ VecTile(const FwdArgs<TIn> &args, int row, int tile)
         : a(args), r(row), W((int)args.W), C(args.C), N(args.N) {
-        const RowGeo rg = row_geo(r, W);
+        const RowGeo rg = GEN ? RowGeo{0, (W + 3) / 4} : row_geo(r, W);
         ca = rg.ca;
         ng = rg.ng;
         rstep = a.in_plane;
@@ -439,7 +458,7 @@ struct VecTile {
         wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
         lane = (int)threadIdx.x & 63;
         int base = tile * BLOCK * G;
-        if constexpr (VOL) {
+        if constexpr (VOL && !GEN) {
             // shift the row's tile grid back by the groups that lie between
             // the previous 128-byte boundary of the volume and the row's
             // first group, so that each wavefront's 1 KB stores of a plane
@@ -453,9 +472,10 @@ struct VecTile {
         }
         alive = base + (VOL ? 64 : 64 * G) * wv < ng;
         // the plane pitch is a multiple of 4, so every plane's row start has
-        // this residue
+        // this residue (GEN: plane 0's, counted from an aligned address)
         constexpr int K = Win::kAlign;
-        gpar = (int)(((int64_t)r * a.in_row) & (K - 1));
+        gpar = (int)(((int64_t)r * a.in_row +
+                      (GEN ? (int64_t)((uintptr_t)a.in / sizeof(TIn)) : 0)) & (K - 1));
         lo_off = -8 + ((K - (gpar + 8) % K) % K);
         hi_off = C - 1 - ((C - 1 + gpar) & (K - 1));
         // plane pitch >= 8: only plane 0 can start closer than 8 elements to
@@ -484,14 +504,19 @@ struct VecTile {
                 // lanes before the row's first group (an aligned tile grid)
                 // repeat it, as lanes past the last repeat the last
                 const int w0 = base + 64 * wv + BLOCK * g;
-                gi[g] = max(0, min(base + (int)threadIdx.x + BLOCK * g, ng - 1));
-                gfirst[g] = max(0, min(w0, ng - 1));
-                glast[g] = max(0, min(w0 + 63, ng - 1));
+                gx[g] = 4 * max(0, min(base + (int)threadIdx.x + BLOCK * g, ng - 1));
+                pfirst[g] = 4 * max(0, min(w0, ng - 1));
+                plast[g] = 4 * max(0, min(w0 + 63, ng - 1));
             } else {
                 const int w0 = base + 64 * G * wv + g;
-                gi[g] = min(w0 + G * lane, ng - 1);
-                gfirst[g] = min(w0, ng - 1);
-                glast[g] = min(w0 + G * 63, ng - 1);
+                gx[g] = 4 * min(w0 + G * lane, ng - 1);
+                pfirst[g] = 4 * min(w0, ng - 1);
+                plast[g] = 4 * min(w0 + G * 63, ng - 1);
+            }
+            if constexpr (GEN) {
+                gx[g] = min(gx[g], W - 4);
+                pfirst[g] = min(pfirst[g], W - 4);
+                plast[g] = min(plast[g], W - 4);
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -501,7 +526,15 @@ struct VecTile {
         }
     }
 
-    __device__ __forceinline__ int xcol(int g) const { return ca + 4 * gi[g]; }
+    // lo_off and hi_off of a plane (GEN: with its row start's parity)
+    __device__ __forceinline__ int lo_of(int v) const {
+        return GEN && Win::kAlign == 2 ? -8 + (v & 1) : lo_off;
+    }
+    __device__ __forceinline__ int hi_of(int v) const {
+        return GEN && Win::kAlign == 2 ? C - 1 - ((C - 1 + v) & 1) : hi_off;
+    }
+
+    __device__ __forceinline__ int xcol(int g) const { return ca + gx[g]; }
 
     // Pacing position (in plane-groups) of chunk plane li of group g in the
     // chunk at c0: every earlier chunk is full, so G * c0 plane-groups lie
@@ -510,15 +543,15 @@ struct VecTile {
         return c0 * G + g * cn + li;
     }
 
-    // Positions [s0 + 4 gfirst, s0 + 4 glast + 5) of the wavefront's group g.
+    // Positions [s0 + pfirst, s0 + plast + 5) of the wavefront's group g.
     __device__ __forceinline__ int cls_of(int s0, int g) const {
-        return cls_range(s0 + 4 * gfirst[g], s0 + 4 * glast[g] + 5);
+        return cls_range(s0 + pfirst[g], s0 + plast[g] + 5);
     }
 
     // All the wavefront's positions (groups side by side: group 0 holds the
     // lowest column, group G - 1 the highest).
     __device__ __forceinline__ int cls_span(int s0) const {
-        return cls_range(s0 + 4 * gfirst[0], s0 + 4 * glast[G - 1] + 5);
+        return cls_range(s0 + pfirst[0], s0 + plast[G - 1] + 5);
     }
 
     __device__ __forceinline__ int cls_range(int q0, int q1) const {
@@ -543,9 +576,13 @@ struct VecTile {
         // clamp there
         const int s0l = ca - pc.k - 1;
         const int s0 = s0l < -(1 << 28) ? -(1 << 28) : (s0l > (1 << 28) ? (1 << 28) : s0l);
-        const int sh = (gpar + s0) & (Win::kAlign - 1);
         ls0 = s0;
-        lwin = (s0 - sh) * 2 + sh;
+        if constexpr (GEN) {
+            lwin = s0 * 2 + ((gpar + (int)((int64_t)n * a.in_plane)) & (Win::kAlign - 1));
+        } else {
+            const int sh = (gpar + s0) & (Win::kAlign - 1);
+            lwin = (s0 - sh) * 2 + sh;
+        }
         lwlo = pc.wlo;
         lwhi = pc.whi;
     }
@@ -560,13 +597,26 @@ struct VecTile {
         }
     }
 
+    // First needed pixel's place in the window of group g (v the plane's
+    // packed start/shift), and that pixel's position in the row.
+    __device__ __forceinline__ int win_shift(int g, int v) const {
+        return GEN ? (((v >> 1) + v + gx[g]) & (Win::kAlign - 1)) : (v & 1);
+    }
+    __device__ __forceinline__ int first_px(int g, int v) const {
+        return (v >> 1) + (GEN ? 0 : (v & 1)) + gx[g];
+    }
+
     // Window of one plane: the packed start/shift v, clamped into [lo, hi]
     // when MASK (lanes reaching outside the row only read values that are
     // masked afterwards).
     template <bool MASK>
     __device__ __forceinline__ void fetch(int g, const TIn *rp, int v, Win &w) const {
-        int off = (v >> 1) + 4 * gi[g];
-        if (MASK) off = off < lo_off ? lo_off : (off > hi_off ? hi_off : off);
+        int off = (v >> 1) + gx[g];
+        if constexpr (GEN) off -= win_shift(g, v);
+        if (MASK) {
+            const int lo = lo_of(v), hi = hi_of(v);
+            off = off < lo ? lo : (off > hi ? hi : off);
+        }
         w.load(bounded(rp + off, Win::kLen, a.in - a.in_lo, a.in + a.in_hi));
     }
 
@@ -574,11 +624,10 @@ struct VecTile {
     template <bool MASK>
     __device__ __forceinline__ void compute(int g, const Win &w, int v, float wlo, float whi,
                                             float d[4]) {
-        const int sh = v & 1;
         float vv[5];
-        w.extract(sh, vv);
+        w.extract(win_shift(g, v), vv);
         if (MASK) {
-            const int p = (v >> 1) + sh + 4 * gi[g];
+            const int p = first_px(g, v);
 #pragma unroll
             for (int i = 0; i < 5; ++i)
                 if ((unsigned)(p + i) >= (unsigned)C) vv[i] = 0.0f;
@@ -599,18 +648,19 @@ struct VecTile {
         constexpr int K = Win::kAlign;
         const TIn *rp = rp0 + (int64_t)n * rstep;
         const int v = __builtin_amdgcn_readlane(win, li);
-        const int sh = v & 1;
+        const int sh = win_shift(g, v);
         const float wlo = lane_f(wlo_l, li), whi = lane_f(whi_l, li);
-        const int off = (v >> 1) + 4 * gi[g];
-        const int p = off + sh;
-        int lo = lo_off, hi = hi_off;
+        const int p = first_px(g, v), off = p - sh;
+        int lo = lo_of(v), hi = hi_of(v);
+        // residue of this plane's row start
+        const int par = GEN ? (v & 1) : gpar;
         if (n == first_special || n == last_special) {
             // the readable extent [in - in_lo, in + in_hi), as window starts
             // of this row with the load's alignment
             const int64_t grow = rp - a.in;
             int64_t lo_ok = -grow - a.in_lo, hi_ok = a.in_hi - Win::kLen - grow;
-            lo_ok += (K - ((grow + lo_ok) % K + K) % K) % K;
-            hi_ok -= ((grow + hi_ok) % K + K) % K;
+            lo_ok += (par + lo_ok) & (K - 1);
+            hi_ok -= (par + hi_ok) & (K - 1);
             lo = (int)(lo_ok > (int64_t)lo ? lo_ok : (int64_t)lo);
             hi = (int)(hi_ok < (int64_t)hi ? hi_ok : (int64_t)hi);
         }
@@ -633,8 +683,9 @@ struct VecTile {
     // ---- with a volume ---------------------------------------------------
 
     __device__ __forceinline__ void store(int g, float *orow, const float d[4]) const {
-        store_f32x4<NT>(bounded(orow + xcol(g), 4, a.vol, a.vol + (int64_t)N * a.vol_plane),
-                        f32x4{d[0], d[1], d[2], d[3]});
+        store_f32x4<NT, std::conditional_t<GEN, f32x4_any, f32x4>>(
+            bounded(orow + xcol(g), 4, a.vol, a.vol + (int64_t)N * a.vol_plane),
+            f32x4{d[0], d[1], d[2], d[3]});
     }
 
     // Chunk planes [l0, l1) of a chunk of cn planes for group g,
@@ -958,8 +1009,9 @@ struct VecTile {
 // Two pixel loads per plane, issued UNR planes ahead of the stores.  Same
 // per-voxel arithmetic and plane order as every other path.  Few lanes
 // trickle through the planes beside the paced tiles for most of the
-// launch; a burst of edge work at the start (the wavefront form below)
-// puts the tiles behind their pacing schedule for good.
+// launch; a burst of edge work at the start (a wavefront per column, its
+// lanes on 64 planes at a time) puts the tiles behind their pacing schedule
+// for good.
 template <typename TIn, int UNR, bool NT>
 __device__ __forceinline__ void fwd_edge_lane(const FwdArgs<TIn> &a, int e) {
     const int W = (int)a.W, C = a.C;
@@ -1021,54 +1073,6 @@ __device__ __forceinline__ void fwd_edge_lane(const FwdArgs<TIn> &a, int e) {
     if (a.pmax) *bounded(a.pmax + o, 1, a.pmax, a.pmax + rw) = mx;
 }
 
-// Edge columns of launches without a volume (the at most 3 unaligned columns at each end of every row,
-// present only when W is not a multiple of 4, and then at least one per
-// row): wavefront e handles slot e % 6 of row e / 6 (empty slots exit at
-// once).  Its lanes take 64 planes at a time, one plane each: coefficients,
-// the two pixel loads and the volume store run in parallel; the FP64 sum
-// then adds the chunk's values in plane order, lane 0 first, as every other
-// path does, and the maximum takes them in the same pass.  (One lane per
-// column walking every plane alone took about 250 us for 512 planes, longer
-// than the rest of a projections-only launch.)
-template <typename TIn, bool NT>
-__device__ __forceinline__ void fwd_edge_wave(const FwdArgs<TIn> &a, int64_t e) {
-    const int W = (int)a.W, C = a.C, N = a.N;
-    const int r = (int)(e / 6);
-    if (r >= a.R) return;
-    const RowGeo rg = row_geo(r, W);
-    const int x = edge_col(rg, W, (int)(e - 6 * (e / 6)));
-    if (x < 0) return;
-    const int lane = (int)threadIdx.x & 63;
-    const int64_t ostep = a.vol_plane;
-    const TIn *rp = a.in + (int64_t)r * a.in_row;
-    float *op = a.vol ? a.vol + (int64_t)r * W + x : nullptr;
-    double acc = 0.0;
-    float mx = -__builtin_huge_valf();
-    for (int c0 = 0; c0 < N; c0 += 64) {
-        const int cn = min(64, N - c0);
-        const int n = min(c0 + lane, N - 1);
-        const PlaneCoef pc = plane_coef(a.offs, a.shift, a.origin, n);
-        const int64_t i = (int64_t)x - pc.k;
-        const TIn *row =
-            bounded(rp + (int64_t)n * a.in_plane, C, a.in - a.in_lo, a.in + a.in_hi);
-        const float d = fmaf(pc.whi, load_px(row, i, (int64_t)C),
-                             pc.wlo * load_px(row, i - 1, (int64_t)C));
-        if (op && lane < cn)
-            store_f32<NT>(bounded(op + (int64_t)n * ostep, 1, a.vol, a.vol + (int64_t)N * ostep),
-                          d);
-        for (int l = 0; l < cn; ++l) {
-            const float dl = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d), l));
-            acc += (double)dl;
-            mx = fmaxf(mx, dl);
-        }
-    }
-    if (lane == 0) {
-        const int64_t o = (int64_t)r * W + x, rw = (int64_t)a.R * W;
-        if (a.psum) *bounded(a.psum + o, 1, a.psum, a.psum + rw) = (float)acc;
-        if (a.pmax) *bounded(a.pmax + o, 1, a.pmax, a.pmax + rw) = mx;
-    }
-}
-
 // Plain launches: one workgroup per (row, tile); vector launches add
 // `edge_blocks` workgroups for the edge columns.
 template <typename TIn, int BLOCK, int J, bool NT>
@@ -1092,19 +1096,18 @@ __device__ __forceinline__ int middle_out(int k, int T) {
 // the heaviest tiles start first (in a uniform scan a column tile meets the
 // most planes at the frame's centre, the fewest at its ends) and lighter
 // ones fill in behind them.
-template <typename TIn, int BLOCK, int G, int UNR, bool NT, bool VOL>
+template <typename TIn, int BLOCK, int G, int UNR, bool NT, bool VOL, bool GEN>
 __device__ __forceinline__ void fwd_vec_block(const FwdArgs<TIn> &a, int tiles_x, int64_t b) {
     // the edge columns' workgroups come first: they are short and start
     // with the first wave of tiles instead of waiting for free slots
-    const int64_t eb = a.edge_wg;
-    if (b < eb) {
-        if constexpr (VOL)
+    if constexpr (VOL && !GEN) {
+        const int64_t eb = a.edge_wg;
+        if (b < eb) {
             fwd_edge_lane<TIn, UNR, NT>(a, (int)(b * BLOCK + threadIdx.x));
-        else
-            fwd_edge_wave<TIn, NT>(a, b * (BLOCK / 64) + ((int)threadIdx.x >> 6));
-        return;
+            return;
+        }
+        b -= eb;
     }
-    b -= eb;
     {
         int r, xt;
         if constexpr (VOL) {
@@ -1115,7 +1118,7 @@ __device__ __forceinline__ void fwd_vec_block(const FwdArgs<TIn> &a, int tiles_x
             r = (int)(b - (int64_t)k * a.R);
             xt = middle_out(k, tiles_x);
         }
-        VecTile<TIn, BLOCK, G, UNR, NT, VOL> vt(a, r, xt);
+        VecTile<TIn, BLOCK, G, UNR, NT, VOL, GEN> vt(a, r, xt);
         vt.run();
     }
 }
@@ -1136,7 +1139,7 @@ constexpr int vec_waves_per_eu(int g, int unr, bool vol, int in_bytes) {
     return w > 8 ? 8 : (w < 1 ? 1 : w);
 }
 
-template <typename TIn, int BLOCK, int G, int UNR, bool NT, bool VOL>
+template <typename TIn, int BLOCK, int G, int UNR, bool NT, bool VOL, bool GEN>
 __global__ __launch_bounds__(BLOCK, vec_waves_per_eu(G, UNR, VOL, (int)sizeof(TIn))) void k_forward_vec(
     FwdArgs<TIn> a, int tiles_x) {
     // edge-column workgroups first, in dispatch order (spread over the
@@ -1144,7 +1147,7 @@ __global__ __launch_bounds__(BLOCK, vec_waves_per_eu(G, UNR, VOL, (int)sizeof(TI
     // XCD gets a contiguous range of them
     const int64_t eb = a.edge_wg, d = blockIdx.x;
     const int64_t lb = (VOL && d >= eb) ? eb + xcd_remap(d - eb, (int64_t)gridDim.x - eb) : d;
-    fwd_vec_block<TIn, BLOCK, G, UNR, NT, VOL>(a, tiles_x, lb);
+    fwd_vec_block<TIn, BLOCK, G, UNR, NT, VOL, GEN>(a, tiles_x, lb);
 }
 
 // Job record of the persistent ragged-batch kernel (device-resident table).
@@ -1204,8 +1207,12 @@ __global__ __launch_bounds__(BLOCK, vec_waves_per_eu(PT >= 8 ? 2 : 1, UNR, VOL, 
         a.align_tiles = 0;
         const int64_t lt = t - jb.tile_begin;
         if constexpr (PT >= 4) {
-            if (jb.vec) {
-                fwd_vec_block<uint16_t, BLOCK, PT / 4, UNR, NT, VOL>(a, jb.tiles_x, lt);
+            if (jb.vec == VEC_ALIGNED) {
+                fwd_vec_block<uint16_t, BLOCK, PT / 4, UNR, NT, VOL, false>(a, jb.tiles_x, lt);
+                continue;
+            }
+            if (jb.vec == VEC_GENERAL) {
+                fwd_vec_block<uint16_t, BLOCK, PT / 4, UNR, NT, VOL, true>(a, jb.tiles_x, lt);
                 continue;
             }
         }

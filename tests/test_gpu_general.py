@@ -1,0 +1,63 @@
+"""Frames whose rows, planes or buffers share no 16-byte phase: the vector
+kernel's general form against the scalar kernel (2 columns per thread, pinned
+to the oracle by the forward tests), bitwise -- both do the same arithmetic in
+the same order."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2211_00645_amd as dsk
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+SCALAR = dict(block=64, per_thread=2, unroll=1)
+
+
+def _stack(shape, dtype, off, seed):
+    n = shape[0] * shape[1] * shape[2]
+    g = torch.Generator().manual_seed(seed)
+    flat = torch.randint(0, 65536, (n + off,), generator=g, dtype=torch.int32)
+    flat = flat.to(torch.uint16) if dtype == "u16" else flat.float() * 0.37
+    return flat.to(DEV)[off:].view(shape)
+
+
+@pytest.mark.parametrize("dtype", ["u16", "f32"])
+@pytest.mark.parametrize("shape,shift,off", [
+    ((5, 3, 7), 0.4, 0),          # odd plane pitch, one partial group past the first
+    ((9, 5, 4), 0.0, 1),          # width 4: one group, every plane inside
+    ((6, 7, 251), 1.3, 3),        # last group moved back across a tile's end
+    ((67, 3, 255), 0.51, 0),      # two chunks of planes, widths around a tile
+    ((130, 5, 61), -2.7, 1),      # reversed scan, runs of padding
+    ((70, 9, 333), 5.9, 2),
+    ((3, 33, 1021), 0.9, 5),
+])
+def test_general_equals_scalar(shape, shift, off, dtype):
+    st = _stack(shape, dtype, off, 11)
+    rng = np.random.default_rng(3)
+    for offs in (np.arange(shape[0]) * shift, np.arange(shape[0]) * shift + rng.normal(0, 1.5, shape[0]),
+                 rng.permutation(shape[0]) * shift):
+        for pad in (0, 2):        # a frame that clips or pads the grid
+            w, b = dsk.plan(shape, offsets=offs)
+            kw = dict(offsets=offs, origin=b + pad, width=max(4, w - pad))
+            for vol in (True, False):
+                ref = dsk.deskew(st, vol=vol, tune=SCALAR, **kw)
+                for tune in (None, dict(unroll=4), dict(per_thread=8, block=256),
+                             dict(unroll=1, pace_gbs=400, nt_store=0)):
+                    out = dsk.deskew(st, vol=vol, tune=tune, **kw)
+                    torch.cuda.synchronize()
+                    for k in ("vol", "psum", "pmax"):
+                        assert (k in out) == (k in ref)
+                        if k in ref:
+                            assert torch.equal(out[k], ref[k]), (k, vol, tune, pad)
+
+
+def test_volume_off_alignment():
+    st = _stack((12, 6, 90), "u16", 0, 5)
+    w, b = dsk.plan((12, 6, 90), shift=dsk.shift_px(30.0, 0.4, 0.115))
+    ref = dsk.deskew(st, 30.0, 0.4, 0.115, tune=SCALAR)
+    buf = torch.empty(12 * 6 * w + 3, device=DEV)
+    for off in (1, 2, 3):
+        vol = buf[off:off + 12 * 6 * w].view(12, 6, w)
+        dsk.deskew(st, 30.0, 0.4, 0.115, out={"vol": vol})
+        torch.cuda.synchronize()
+        assert torch.equal(vol, ref["vol"]), off
