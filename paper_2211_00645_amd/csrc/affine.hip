@@ -9,13 +9,20 @@
 //
 // The output is several times the remap's volume and each output row
 // crosses many images, so a plain gather would fetch a cache line per pixel.
-// The kernels keep the images a 64-column strip needs in an LDS ring while
-// they sweep y.  The main one (k_affine_rows) sweeps four rows of a strip at
-// once, so that each voxel's weights, which depend on (y, z) only, serve four
-// voxels; k_affine_ring (one row, a lane per column) covers the layouts it
-// does not take, and the one-shot kernel (k_affine, one lane per 4 output
-// columns in output order) the geometries no ring takes (the band moving a
-// whole image or more per y, or wider than the ring).
+// The strip kernel (k_affine_strip) keeps the images a 64-column strip needs
+// in an LDS ring while a workgroup sweeps y, 4 rows of the strip at once, so
+// that each voxel's weights, which depend on (y, z) only, serve four voxels.
+// The one-shot kernel (k_affine, one lane per 4 output columns in output
+// order) covers the geometries whose images no ring holds (grids as coarse as
+// the scan, very fine scans) and rows of one column.
+//
+// Bound: writes to HBM in this output order (a kernel of the same stores and
+// nothing else: 2.70 ms on the 512x512x2048 stack, 5.4 TB/s).  Measured:
+//   512x512x2048, 0.4 um, 15.6 GB: 3.24 ms, 4.81 TB/s (one wavefront per
+//     4-row strip with a float ring: 3.40; one row: 4.40; one-shot: 17.4)
+//   150x203x1001, 45 deg, 0.2 um, 0.85 GB: 0.205 ms, 4.1 TB/s (one-shot, the
+//     only kernel that took it: 1.345)
+//   200x301x777, 35 deg, 0.6 um, 1.66 GB: 0.364 ms, 4.6 TB/s
 #include <cmath>
 #include <cstdint>
 
@@ -89,405 +96,271 @@ __global__ __launch_bounds__(kAffBlock) void k_affine(AffArgs<TIn> a) {
     }
 }
 
-// Ring kernel: one wavefront per (y chunk, row x, 64 columns), sweeping its
-// y chunk in the direction in which u grows.  The images the 64 columns
-// need at one y form a band of about 64 |uz| + 2 consecutive images, moving
-// by |uy| < 1 images per y.  The band lives in an LDS ring of 32 image rows
-// (64 floats each, row n mod 32); each image row enters once, with one
-// coalesced 128-byte load issued a few steps before its first use and
-// written to the ring when it is consumed.  Every voxel then reads its two
-// images from LDS instead of gathering them from L2.
-constexpr int kAffAhead = 8;
+// Strip kernel: a workgroup of 4 wavefronts sweeps a y range of one strip of
+// kStripRows rows x kStripCols columns, kChunk y values at a time, in the
+// direction in which u grows.  The images a chunk needs form a band of
+// consecutive images, as wide as the strip's columns and the chunk's y values
+// spread over; it lives in an LDS ring of kRing images (image n in slot n mod
+// kRing) holding the raw 16-bit pixels, the strip's rows interleaved, so that
+// one 8-byte LDS read returns a column of an image in all rows.
+//  * A voxel's weights depend on (y, z) only: 16 lanes per y value, 4
+//    adjacent columns each, compute them once, in FP64, for all kStripRows
+//    rows, and write each row's 4 columns with one 16-byte store.
+//  * The images the next chunk adds (at most kNewImages) are loaded into
+//    registers before a chunk is computed and enter the ring after it, so
+//    the loads are in flight while the chunk's voxels are written; every line
+//    of the stack is read once (a ring that follows the columns' diagonal, and
+//    so fits any strip width, reads each line in 3-4 chunks and was slower:
+//    3.95 ms against 3.2 on the 512x512x2048 stack).
+//  * Column c of the window sits in place (c mod 4) * WC / 4 + c / 4 of its
+//    slot (the 16 lanes of a y value then read 128 consecutive bytes), and odd
+//    slots swap neighbouring 128-byte blocks, so that two y values reading
+//    neighbouring images seldom meet in the same banks.
+//  * PHASE: the volume's rows start at different places of a 128-byte line.
+//    A strip's 256-byte runs would then leave partial lines at both ends,
+//    which cost more than anything else here (150x203x1001, 0.2 um step:
+//    445 us against 216), so a run starts up to 31 columns earlier, at a line boundary;
+//    the strip's rows are taken phase_rows apart, the distance at which rows
+//    have one phase, and keep sharing their weights.  The window is 32
+//    columns wider.
+// Loads take 2 pixels at any 2-byte boundary and a row's partial groups are
+// stored by column, so any column count of at least 2 and any row phase runs
+// here.
+constexpr int kStripRows = 4;
+constexpr int kStripCols = 64;
+constexpr int kRing = 64;
+constexpr int kNewImages = 16;
+constexpr int kStripBlock = 256;
+constexpr int kChunk = 16;
 
-template <typename TIn>
-struct RingArgs {
-    AffArgs<TIn> a;
-    int64_t ychunk;       // y values per wavefront
-    int32_t ztiles;       // 64-column tiles per row
-};
+constexpr int strip_window(bool phase) { return kStripCols + (phase ? 32 : 0); }
 
-// YQ y values per step (1, or 4 when the band moves less than half an
-// image per y, i.e. at most 2 new images per step); AHEAD steps of
-// look-ahead.  The ring has 32 rows plus a copy of row 0 after row 31, so
-// the two images a voxel needs are always in consecutive rows.  The host
-// keeps every u within +-1e9, so floors fit an int.
-template <typename TIn, int YQ, int AHEAD>
-__global__ __launch_bounds__(64) void k_affine_ring(RingArgs<TIn> ra) {
-    constexpr int NF = YQ == 1 ? 1 : 2;        // fetches per step
-    __shared__ float ring[33 * 64];
-    const AffArgs<TIn> &a = ra.a;
-    const int lane = (int)threadIdx.x;
-    const int64_t b = blockIdx.x;
-    const int64_t per_chunk = (int64_t)a.R * ra.ztiles;
-    const int64_t yc = b / per_chunk;
-    const int64_t rem = b - yc * per_chunk;
-    const int x = (int)(rem / ra.ztiles);
-    const int zb = 64 * (int)(rem - (int64_t)x * ra.ztiles);
-    const int ze = zb + 63 < a.C ? zb + 63 : a.C - 1;
-    const bool zok = zb + lane < a.C;
-    const int zc = zok ? zb + lane : ze;       // the column this lane reads and writes
-    const int64_t y_lo = yc * ra.ychunk;
-    const int64_t y_hi = (y_lo + ra.ychunk < a.ny ? y_lo + ra.ychunk : a.ny);
-    const int ny_c = (int)(y_hi - y_lo);
-    const int steps = (ny_c + YQ - 1) / YQ;
-    // y runs in the direction in which u grows; u = P(y) - z uz, where the
-    // chain P(next y) = P(y) + |uy| gives the one value both the band
-    // bookkeeping and the voxels use, so they always agree on which images
-    // are needed
-    const bool up = a.uy > 0.0;
-    const int64_t y_first = up ? y_lo : y_hi - 1;
-    const double ds = fabs(a.uy);
-    const double uzl = __dmul_rn((double)zc, a.uz);
-    const double uzb = __dmul_rn((double)zb, a.uz), uze = __dmul_rn((double)ze, a.uz);
-    const double uz_min = uzb < uze ? uzb : uze, uz_max = uzb < uze ? uze : uzb;
-    auto fl = [](double v) { return (int)floor(v); };
-    // P of the first y of each of the next AHEAD steps, and of step AHEAD
-    double Pq[AHEAD];
-    Pq[0] = __dadd_rn(a.u0, __dmul_rn((double)y_first, a.uy));
-#pragma unroll
-    for (int k = 1; k < AHEAD; ++k) {
-        double p = Pq[k - 1];
-#pragma unroll
-        for (int i = 0; i < YQ; ++i) p = __dadd_rn(p, ds);
-        Pq[k] = p;
-    }
-    double Pa = Pq[AHEAD - 1];
-#pragma unroll
-    for (int i = 0; i < YQ; ++i) Pa = __dadd_rn(Pa, ds);
-    // last P of a step whose first P is p
-    auto last_p = [&](double p) {
-#pragma unroll
-        for (int i = 1; i < YQ; ++i) p = __dadd_rn(p, ds);
-        return p;
-    };
-    // images outside the stack read image 0 or N-1 and enter the ring
-    // scaled by 0, so every fetch is one unconditional coalesced load and
-    // the ring holds zeros for them
-    const TIn *rowx = a.in + (int64_t)x * a.C;    // wave-uniform base
-    const int64_t plane = (int64_t)a.R * a.C;
-    auto load = [&](int n) {
-        const TIn *base = rowx + (int64_t)(n < 0 ? 0 : (n >= a.N ? a.N - 1 : n)) * plane;
-        return base[zc];
-    };
-    auto scale = [&](int n) { return (n >= 0 && n < a.N) ? 1.0f : 0.0f; };
-    auto put = [&](int m, float v) {
-        const int r = m & 31;
-        ring[r * 64 + lane] = v;
-        if (r == 0) ring[32 * 64 + lane] = v;
-    };
-    // fill: the band of the first AHEAD steps, 8 loads at a time
-    int have;
-    {
-        const int lo0 = fl(__dsub_rn(Pq[0], uz_max));
-        const int last = steps - 1 < AHEAD - 1 ? steps - 1 : AHEAD - 1;
-        const int top = fl(__dsub_rn(last_p(Pq[last]), uz_min)) + 1;
-        for (int n = lo0; n <= top; n += 8) {
-            TIn t[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) t[i] = load(n + i <= top ? n + i : top);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int m = n + i <= top ? n + i : top;
-                put(m, (float)t[i] * scale(m));
-            }
-        }
-        have = top;
-    }
-    // per step exactly NF fetches and YQ stores: the images the step AHEAD
-    // later first needs, or again the newest image (its ring row is
-    // rewritten with the same values)
-    TIn q[AHEAD][NF];
-    int qn[AHEAD][NF];
-#pragma unroll
-    for (int k = 0; k < AHEAD; ++k)
-#pragma unroll
-        for (int i = 0; i < NF; ++i) {
-            q[k][i] = 0;
-            qn[k][i] = have;
-        }
-    const int64_t ostep = (up ? 1 : -1) * (int64_t)a.R * a.C;
-    float *orow = a.vol + (y_first * a.R + x) * (int64_t)a.C;   // wave-uniform
+// 32 KB of LDS each, 48 KB with the wider window
+constexpr int strip_wg_per_cu(bool phase) { return phase ? 3 : 4; }
 
-    auto step = [&](int k, int j, bool tail) {
-        // the images fetched AHEAD steps ago enter the ring
-        if (j >= AHEAD) {
-#pragma unroll
-            for (int i = 0; i < NF; ++i) put(qn[k][i], (float)q[k][i] * scale(qn[k][i]));
-        }
-        const double p0 = Pq[k];                // P of this step's first y
-        int m = have;
-        if (j + AHEAD < steps) {
-            const int h = fl(__dsub_rn(last_p(Pa), uz_min)) + 1;  // leading edge
-            m = h > have ? h : have;
-        }
-        Pq[k] = Pa;
-#pragma unroll
-        for (int i = 0; i < YQ; ++i) Pa = __dadd_rn(Pa, ds);
-        // at most NF new images: have + 1 .. m
-#pragma unroll
-        for (int i = 0; i < NF; ++i) {
-            const int mi = have + 1 + i <= m ? have + 1 + i : m;
-            q[k][i] = load(mi);
-            qn[k][i] = mi;
-        }
-        have = m;
-        {
-            double p = p0;
-#pragma unroll
-            for (int i = 0; i < YQ; ++i) {
-                if (i) p = __dadd_rn(p, ds);
-                const double u = __dsub_rn(p, uzl);
-                const double fi = floor(u);
-                const int r = (int)fi & 31;
-                const double f = __dsub_rn(u, fi);
-                // both weights rounded once from FP64 (1 - wlo in FP32 would
-                // lose the relative precision of a small 1 - f)
-                const float wlo = (float)f, whi = (float)__dsub_rn(1.0, f);
-                const float lo = ring[r * 64 + lane];
-                const float hi = ring[r * 64 + 64 + lane];
-                // lanes past the last column repeat the last column's value
-                // to its address: one unconditional store per y
-                if (!tail || j * YQ + i < ny_c)
-                    store_f32<true>(orow + zc, fmaf(wlo, hi, whi * lo));
-                orow += ostep;
-            }
-        }
-    };
-    const int full = (ny_c / YQ) / AHEAD * AHEAD;   // steps with all YQ y values, whole groups
-    for (int j0 = 0; j0 < full; j0 += AHEAD) {
-#pragma unroll
-        for (int k = 0; k < AHEAD; ++k) step(k, j0 + k, false);
-    }
-#pragma unroll
-    for (int k = 0; k < AHEAD; ++k)
-        if (full + k < steps) step(k, full + k, true);
-}
+constexpr int64_t kCachedBytes = 256000000;
 
-// Row kernel: persistent wavefronts, each taking work items (y range, strip
-// of kAffRows rows x 64 columns) in turn, consecutive wavefronts on
-// neighbouring strips of one y range, so that the wavefronts write
-// neighbouring output rows of the same planes.  Each sweeps its y range in
-// the direction in which u grows, 4 y values per step:
-//  * the weights of a voxel depend on (y, z) only: lane group y (16 lanes,
-//    4 adjacent columns each) computes them once, in FP64 as the ring
-//    kernel does, and applies them to all kAffRows rows;
-//  * the rows share one LDS ring of 32 image rows with the rows interleaved
-//    (ring[((n mod 32) * 64 + column) * kAffRows + row]), so one 16-byte LDS
-//    read returns an image's value in all rows and one 16-byte write enters
-//    it;
-//  * the at most 2 images a step needs first arrive in one 4-byte load per
-//    row: the wavefront's halves read the two images, 2 columns per lane,
-//    AHEAD steps before the step that needs them;
-//  * the y chain P(y + 1) = P(y) + |uy| restarts from the exact
-//    u0 + y uy every kAffRestart values of the sweep (as the ring kernel's
-//    512-y work items do), so its rounding never accumulates over more than
-//    that many adds.
-// Requires (host): C a multiple of 4, the stack 4-byte and the volume 16-byte
-// aligned, at most 2 new images per step and the band within the ring
-// (the YQ = 4 ring conditions).  Rows past the last repeat the last row
-// (identical values to identical addresses).
-constexpr int kAffRows = 4;
-constexpr int kAffRestart = 512;
-constexpr int kAffRowsAhead = 4;
-// Workgroups per compute unit: the 32 KB ring allows 5; 4 (one wavefront
-// per SIMD) gave each of them the same number of work items on the
-// 512x512x2048 stack (4096 strips over 1024 wavefronts).  Measured there:
-// 3.37 ms against 4.40 ms for the lane-per-column ring kernel.
-constexpr int kAffRowsPerCU = 4;
-
-struct RowsArgs {
+struct StripArgs {
     AffArgs<uint16_t> a;
-    int64_t ylen;      // y values per work item, a multiple of kAffRestart
-    int64_t strips;    // ceil(R / kAffRows) * ztiles
-    int64_t items;     // strips * ceil(ny / ylen)
+    int64_t ylen;        // y values per workgroup
+    int64_t strips;      // row groups * ztiles
     int32_t ztiles;
+    int32_t phase_rows;  // distance of a strip's rows
 };
 
-__device__ __forceinline__ void affine_rows_item(const AffArgs<uint16_t> &a, float *ring, int x0,
-                                                 int zb, int64_t y_lo, int64_t y_hi) {
-    constexpr int AHEAD = kAffRowsAhead;
-    constexpr int NR = kAffRows;
-    const int lane = (int)threadIdx.x;
-    const int ze = zb + 63 < a.C ? zb + 63 : a.C - 1;
-    // this lane's y within a step and its 4 columns (lanes past the last
-    // group repeat it)
-    const int yq = lane >> 4;
-    const int ngrp = (ze - zb + 1) / 4;
-    const int zq = zb + 4 * ((lane & 15) < ngrp ? (lane & 15) : ngrp - 1);
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32_any __attribute__((aligned(2)));
+
+template <bool PHASE, bool NT>
+__global__ __launch_bounds__(kStripBlock, strip_wg_per_cu(PHASE)) void k_affine_strip(StripArgs sa) {
+    constexpr int NR = kStripRows;
+    constexpr int WC = strip_window(PHASE);
+    constexpr int kSlot = WC * 2;                           // dwords per image
+    constexpr int kPairs = WC / 2;                          // column pairs per image
+    constexpr int kTasks = kNewImages * kPairs / kStripBlock;
+    static_assert(kTasks * kStripBlock == kNewImages * kPairs, "whole load rounds");
+    __shared__ __align__(16) uint32_t ring[kRing * kSlot];
+    const AffArgs<uint16_t> &a = sa.a;
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    // neighbouring strips of a row on one XCD, whose L2 joins the lines they
+    // share
+    const int64_t bid = xcd_remap(blockIdx.x, gridDim.x);
+    const int64_t yc = bid / sa.strips, st = bid - yc * sa.strips;
+    const int xi = (int)(st / sa.ztiles);
+    const int S = PHASE ? sa.phase_rows : 1;
+    const int x0 = xi / S * (NR * S) + xi % S;
+    if (x0 >= a.R) return;
+    const int zb = kStripCols * (int)(st - (int64_t)xi * sa.ztiles);
+    const int wb = PHASE ? zb - 32 : zb;                    // window's first column
+    const int64_t y_lo = yc * sa.ylen;
+    const int64_t y_hi = y_lo + sa.ylen < a.ny ? y_lo + sa.ylen : a.ny;
     const int ny_c = (int)(y_hi - y_lo);
-    const int steps = (ny_c + 3) / 4;
+    const int chunks = (ny_c + kChunk - 1) / kChunk;
     const bool up = a.uy > 0.0;
     const int64_t y_first = up ? y_lo : y_hi - 1;
-    const double ds = fabs(a.uy);
+    const int ydir = up ? 1 : -1;
+    const int64_t plane = (int64_t)a.R * a.C;
+    // u of column 0 at sweep index i
+    auto P = [&](int i) {
+        const int64_t y = y_first + (int64_t)ydir * i;
+        return __dadd_rn(a.u0, __dmul_rn((double)y, a.uy));
+    };
+    auto fl = [](double v) { return (int)floor(v); };
+    const int we = wb + WC - 1 < a.C - 1 ? wb + WC - 1 : a.C - 1;
+    const double uzb = __dmul_rn((double)(wb > 0 ? wb : 0), a.uz), uze = __dmul_rn((double)we, a.uz);
+    const double uz_min = uzb < uze ? uzb : uze, uz_max = uzb < uze ? uze : uzb;
+    // last image the chunk whose first sweep index is i needs
+    auto top_of = [&](int i) {
+        return fl(__dsub_rn(P(i + kChunk - 1 < ny_c ? i + kChunk - 1 : ny_c - 1), uz_min)) + 1;
+    };
+
+    // load tasks: (image, column pair), the pair's NR rows each
+    int64_t rowo[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+        rowo[r] = (int64_t)(x0 + r * S < a.R ? x0 + r * S : x0) * a.C;
+    auto load = [&](int n, int pr, uint32_t v[NR]) {
+        // images outside the stack read image 0 or N - 1 and enter as zeros
+        const int64_t nc = n < 0 ? 0 : (n >= a.N ? a.N - 1 : n);
+        const int pz = wb + 2 * pr;
+        const uint16_t *p = a.in + nc * plane + (pz < 0 ? 0 : (pz <= a.C - 2 ? pz : a.C - 2));
+#pragma unroll
+        for (int r = 0; r < NR; ++r) v[r] = *(const u32_any *)(p + rowo[r]);
+    };
+    auto place = [](int n, int c) {   // dword of window column c of image n
+        return (n & (kRing - 1)) * kSlot + 2 * (((c & 3) * (WC / 4) + (c >> 2)) ^ ((n & 1) << 4));
+    };
+    auto put = [&](int n, int pr, const uint32_t v[NR]) {
+        const bool ok = n >= 0 && n < a.N, last_odd = wb + 2 * pr == a.C - 1;
+        uint32_t w[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) w[r] = !ok ? 0u : (last_odd ? v[r] >> 16 : v[r]);
+        *(u32x2 *)(ring + place(n, 2 * pr)) =
+            u32x2{(w[0] & 0xffffu) | (w[1] << 16), (w[2] & 0xffffu) | (w[3] << 16)};
+        *(u32x2 *)(ring + place(n, 2 * pr + 1)) =
+            u32x2{(w[0] >> 16) | (w[1] & 0xffff0000u), (w[2] >> 16) | (w[3] & 0xffff0000u)};
+    };
+
+    // the first chunk's band
+    int have = top_of(0);
+    const int lo0 = fl(__dsub_rn(P(0), uz_max));
+    for (int id = tid; id < (have - lo0 + 1) * kPairs; id += 2 * kStripBlock) {
+        const int id1 = id + kStripBlock;
+        const int n0 = lo0 + id / kPairs, n1 = lo0 + id1 / kPairs;
+        uint32_t v0[NR], v1[NR];
+        load(n0, id % kPairs, v0);
+        load(n1, id1 % kPairs, v1);
+        put(n0, id % kPairs, v0);
+        if (n1 <= have) put(n1, id1 % kPairs, v1);
+    }
+    __syncthreads();
+
+    // this lane's y within a step and its first column (less the row's phase)
+    const int yq = tid >> 4;
+    const int zl = zb + 4 * (lane & 15);
     double uzq[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) uzq[i] = __dmul_rn((double)(zq + i), a.uz);
-    const double uzb = __dmul_rn((double)zb, a.uz), uze = __dmul_rn((double)ze, a.uz);
-    const double uz_min = uzb < uze ? uzb : uze, uz_max = uzb < uze ? uze : uzb;
-    auto fl = [](double v) { return (int)floor(v); };
-    const int64_t plane = (int64_t)a.R * a.C;
-    // loads: half h of the wavefront reads the step's image h, columns
-    // pcol, pcol + 1 (the last pair repeated past the strip's end)
-    const int pl = 2 * (lane & 31);
-    const bool second = lane >= 32;
-    const int pcol = zb + pl <= a.C - 2 ? zb + pl : a.C - 2;
-    const uint16_t *rowp[NR];
-    float *orow[NR];
+    for (int k = 0; k < 4; ++k) uzq[k] = __dmul_rn((double)(zl + k), a.uz);
+    const int64_t row0 = (y_first + (int64_t)ydir * yq) * a.R + x0;
+    float *out = a.vol + row0 * a.C + zl;
+    const int64_t ostep = (int64_t)ydir * kChunk * plane;
+    // columns between the line boundary before the row's start and that start
+    int ph = 0, phstep = 0;
+    if constexpr (PHASE) {
+        ph = (int)(((uintptr_t)a.vol >> 2) + row0 * a.C) & 31;
+        phstep = (int)ostep & 31;
+    }
+    int64_t orow[NR];
+    bool rok[NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-        const int x = x0 + r < a.R ? x0 + r : a.R - 1;
-        rowp[r] = a.in + (int64_t)x * a.C + pcol;
-        orow[r] = a.vol + (y_first * a.R + x) * (int64_t)a.C;
+        orow[r] = (int64_t)r * S * a.C;
+        rok[r] = x0 + r * S < a.R;
     }
-    // images outside the stack read image 0 or N-1 and enter the ring
-    // scaled by 0
-    auto load2 = [&](int r, int m0, int m1) {
-        const int n = second ? m1 : m0;
-        const int64_t nc = n < 0 ? 0 : (n >= a.N ? a.N - 1 : n);
-        return *(const uint32_t *)(rowp[r] + nc * plane);
-    };
-    auto put2 = [&](int m0, int m1, const uint32_t *v) {
-        const int n = second ? m1 : m0;
-        const float sc = (n >= 0 && n < a.N) ? 1.0f : 0.0f;
-        float *p = ring + ((n & 31) * 64 + pl) * NR;
-        f32x4 e, o;
-        e.x = (float)(v[0] & 0xffffu) * sc;
-        e.y = (float)(v[1] & 0xffffu) * sc;
-        e.z = (float)(v[2] & 0xffffu) * sc;
-        e.w = (float)(v[3] & 0xffffu) * sc;
-        o.x = (float)(v[0] >> 16) * sc;
-        o.y = (float)(v[1] >> 16) * sc;
-        o.z = (float)(v[2] >> 16) * sc;
-        o.w = (float)(v[3] >> 16) * sc;
-        *(f32x4 *)p = e;
-        *(f32x4 *)(p + NR) = o;
-    };
-    // the chain: the step prepared next starts at sweep index 4 * prep; each
-    // step's 4 chain values are computed once, when it is prepared AHEAD
-    // steps ahead, and each lane keeps the one of its y
-    double Pc = 0.0, cfirst = 0.0;
-    double Psel[AHEAD];
-    int top = 0;           // last image the prepared step needs
-    auto prepare = [&](int k, int prep) {
-        const int i0 = 4 * prep;
-        const int64_t y = up ? y_first + i0 : y_first - i0;
-        const double c0 = (i0 % kAffRestart == 0) ? __dadd_rn(a.u0, __dmul_rn((double)y, a.uy)) : Pc;
-        const double c1 = __dadd_rn(c0, ds), c2 = __dadd_rn(c1, ds), c3 = __dadd_rn(c2, ds);
-        // this lane's value, picked without a branch (integer selects on the
-        // two halves)
-        int plo = __double2loint(c0), phi = __double2hiint(c0);
-        plo = yq == 1 ? __double2loint(c1) : plo;
-        phi = yq == 1 ? __double2hiint(c1) : phi;
-        plo = yq == 2 ? __double2loint(c2) : plo;
-        phi = yq == 2 ? __double2hiint(c2) : phi;
-        plo = yq == 3 ? __double2loint(c3) : plo;
-        phi = yq == 3 ? __double2hiint(c3) : phi;
-        Psel[k] = __hiloint2double(phi, plo);
-        cfirst = c0;
-        top = fl(__dsub_rn(c3, uz_min)) + 1;
-        Pc = __dadd_rn(c3, ds);
-    };
-    prepare(0, 0);
-    const int lo0 = fl(__dsub_rn(cfirst, uz_max));   // the first step's lowest image
-#pragma unroll
-    for (int k = 1; k < AHEAD; ++k)
-        if (k < steps) prepare(k, k);
-    // fill: the band of the first AHEAD steps, 8 images per round
-    for (int n = lo0; n <= top; n += 8) {
-        uint32_t t[4][NR];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int m0 = n + 2 * i <= top ? n + 2 * i : top;
-            const int m1 = n + 2 * i + 1 <= top ? n + 2 * i + 1 : top;
-#pragma unroll
-            for (int r = 0; r < NR; ++r) t[i][r] = load2(r, m0, m1);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int m0 = n + 2 * i <= top ? n + 2 * i : top;
-            const int m1 = n + 2 * i + 1 <= top ? n + 2 * i + 1 : top;
-            put2(m0, m1, t[i]);
-        }
-    }
-    int have = top;
-    uint32_t q[AHEAD][NR];
-    int qn[AHEAD][2];
-#pragma unroll
-    for (int k = 0; k < AHEAD; ++k) {
-        qn[k][0] = qn[k][1] = have;
-#pragma unroll
-        for (int r = 0; r < NR; ++r) q[k][r] = 0;
-    }
-    const int64_t ostep = (up ? 1 : -1) * plane;
-#pragma unroll
-    for (int r = 0; r < NR; ++r) orow[r] += (int64_t)yq * ostep + zq;
 
-    auto step = [&](int k, int j, bool tail) {
-        // the images fetched AHEAD steps ago enter the ring
-        if (j >= AHEAD) put2(qn[k][0], qn[k][1], q[k]);
-        const double p = Psel[k];
-        int m = have;
-        if (j + AHEAD < steps) {
-            prepare(k, j + AHEAD);
-            m = top > have ? top : have;
+    for (int c = 0; c < chunks; ++c) {
+        const int i0 = c * kChunk;
+        // the images the next chunk adds
+        uint32_t q[kTasks][NR];
+        int top = have;
+        if (c + 1 < chunks) {
+            top = top_of(i0 + kChunk);
+            top = top > have ? top : have;
+#pragma unroll
+            for (int t = 0; t < kTasks; ++t) {
+                const int id = tid + t * kStripBlock, n = have + 1 + id / kPairs;
+                load(n <= top ? n : top, id % kPairs, q[t]);
+            }
         }
-        // at most 2 new images: have + 1 .. m (or again the newest)
-        const int mi0 = have + 1 <= m ? have + 1 : m, mi1 = have + 2 <= m ? have + 2 : m;
+        {
+            const int i = i0 + yq;
+            const double p = P(i);
+            const int zq = zl - ph;
+            float wl[4], wh[4];
+            u32x2 lo[4], hi[4];
 #pragma unroll
-        for (int r = 0; r < NR; ++r) q[k][r] = load2(r, mi0, mi1);
-        qn[k][0] = mi0;
-        qn[k][1] = mi1;
-        have = m;
-        float wl[4], wh[4];
-        f32x4 lo[4], hi[4];
+            for (int k = 0; k < 4; ++k) {
+                const double u =
+                    __dsub_rn(p, PHASE ? __dmul_rn((double)(zq + k), a.uz) : uzq[k]);
+                const double fi = floor(u);
+                const double f = __dsub_rn(u, fi);
+                const int n = (int)fi;
+                // both weights rounded once from FP64
+                wl[k] = (float)f;
+                wh[k] = (float)__dsub_rn(1.0, f);
+                lo[k] = *(const u32x2 *)(ring + place(n, zq + k - wb));
+                hi[k] = *(const u32x2 *)(ring + place(n + 1, zq + k - wb));
+            }
+            f32x4 v[NR];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const double u = __dsub_rn(p, uzq[i]);
-            const double fi = floor(u);
-            const int n0 = (int)fi;
-            const int c = zq - zb + i;
-            const double f = __dsub_rn(u, fi);
-            // both weights rounded once from FP64
-            wl[i] = (float)f;
-            wh[i] = (float)__dsub_rn(1.0, f);
-            lo[i] = *(const f32x4 *)(ring + ((n0 & 31) * 64 + c) * NR);
-            hi[i] = *(const f32x4 *)(ring + (((n0 + 1) & 31) * 64 + c) * NR);
+            for (int k = 0; k < 4; ++k) {
+                v[0][k] = fmaf(wl[k], (float)(hi[k].x & 0xffffu), wh[k] * (float)(lo[k].x & 0xffffu));
+                v[1][k] = fmaf(wl[k], (float)(hi[k].x >> 16), wh[k] * (float)(lo[k].x >> 16));
+                v[2][k] = fmaf(wl[k], (float)(hi[k].y & 0xffffu), wh[k] * (float)(lo[k].y & 0xffffu));
+                v[3][k] = fmaf(wl[k], (float)(hi[k].y >> 16), wh[k] * (float)(lo[k].y >> 16));
+            }
+            if (i < ny_c) {
+                float *o = out - ph;
+                if (zq >= 0 && zq + 4 <= a.C) {
+#pragma unroll
+                    for (int r = 0; r < NR; ++r)
+                        if (rok[r]) store_f32x4<NT, f32x4_any>(o + orow[r], v[r]);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        if (zq + k < 0 || zq + k >= a.C) continue;
+#pragma unroll
+                        for (int r = 0; r < NR; ++r)
+                            if (rok[r]) store_f32<false>(o + orow[r] + k, v[r][k]);
+                    }
+                }
+            }
+            out += ostep;
+            ph = (ph + phstep) & 31;
         }
-        f32x4 v[NR];
+        if (c + 1 < chunks) {
+            __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            v[0][i] = fmaf(wl[i], hi[i].x, wh[i] * lo[i].x);
-            v[1][i] = fmaf(wl[i], hi[i].y, wh[i] * lo[i].y);
-            v[2][i] = fmaf(wl[i], hi[i].z, wh[i] * lo[i].z);
-            v[3][i] = fmaf(wl[i], hi[i].w, wh[i] * lo[i].w);
+            for (int t = 0; t < kTasks; ++t) {
+                const int id = tid + t * kStripBlock, n = have + 1 + id / kPairs;
+                if (n <= top) put(n, id % kPairs, q[t]);
+            }
+            have = top;
+            __syncthreads();
         }
-        if (!tail || j * 4 + yq < ny_c) {
-#pragma unroll
-            for (int r = 0; r < NR; ++r) store_f32x4<true>(orow[r], v[r]);
-        }
-#pragma unroll
-        for (int r = 0; r < NR; ++r) orow[r] += 4 * ostep;
-    };
-    const int full = (ny_c / 4) / AHEAD * AHEAD;   // steps with all 4 y values, whole groups
-    for (int j0 = 0; j0 < full; j0 += AHEAD) {
-#pragma unroll
-        for (int k = 0; k < AHEAD; ++k) step(k, j0 + k, false);
     }
-#pragma unroll
-    for (int k = 0; k < AHEAD; ++k)
-        if (full + k < steps) step(k, full + k, true);
 }
 
-__global__ __launch_bounds__(64) void k_affine_rows(RowsArgs ra) {
-    __shared__ __align__(16) float ring[kAffRows * 32 * 64];
-    for (int64_t it = blockIdx.x; it < ra.items; it += gridDim.x) {
-        const int64_t c = it / ra.strips, s = it - c * ra.strips;
-        const int xi = (int)(s / ra.ztiles);
-        const int zb = 64 * (int)(s - (int64_t)xi * ra.ztiles);
-        const int64_t y_lo = c * ra.ylen;
-        const int64_t y_hi = y_lo + ra.ylen < ra.a.ny ? y_lo + ra.ylen : ra.a.ny;
-        affine_rows_item(ra.a, ring, xi * kAffRows, zb, y_lo, y_hi);
+// y values per workgroup.  Workgroups drift apart in y as they sweep, which
+// scatters the writes, so where the last-level cache holds the stack the y
+// range is cut into parts of at most kPartY values (every part loads its first
+// band anew): 200x301x777 0.404 -> 0.364 ms, 256x256x1000 0.633 -> 0.590,
+// 256x512x1024 (268 MB) 0.636 -> 0.609; from HBM the bands cost more than the
+// drift, and a larger stack is swept whole (512x512x2048, 1.07 GB: 3.23 ms,
+// in parts of 256 3.62).  With fewer than 4 rounds of resident workgroups
+// the range is cut further, into the count of parts that fills the rounds
+// best; a part costs its y values and about 24 more.
+constexpr int64_t kPartY = 256;
+constexpr int64_t kCachedStack = 300000000;
+
+int64_t strip_ylen(int64_t strips, int64_t ny, int wg_per_cu, int64_t stack_bytes) {
+    const int64_t resident = (int64_t)wg_per_cu * device_cus();
+    const int64_t first = stack_bytes <= kCachedStack ? (ny + kPartY - 1) / kPartY : 1;
+    int64_t best = first;
+    if (strips * first >= 4 * resident) return first == 1 ? ny : kPartY;
+    double cost = 1e300;
+    for (int64_t parts = first;
+         parts < first + 32 && (parts == first || ny / parts >= 2 * kChunk); ++parts) {
+        const double len = (double)((ny + parts - 1) / parts);
+        const double rounds = (double)((strips * parts + resident - 1) / resident);
+        const double c = rounds * (len + 24.0);
+        if (c < 0.97 * cost) {
+            cost = c;
+            best = parts;
+        }
     }
+    const int64_t len = (ny + best - 1) / best;
+    return (len + kChunk - 1) / kChunk * kChunk;
 }
 
 bool geom_ok(dsk_geom g) {
@@ -528,50 +401,49 @@ extern "C" int dsk_affine_u16(const uint16_t *in, dsk_dims d, dsk_geom g, double
     const int64_t threads = ny * (int64_t)d.rows * a.zgroups;
     if (threads / kAffBlock >= kMaxI32) return DSK_ESHAPE;
     const dim3 grid((unsigned)((threads + kAffBlock - 1) / kAffBlock));
-    // ring kernels when the band moves less than one image per y and fits
-    // 32 ring rows; otherwise the one-shot kernel
-    // y values per wavefront: long sweeps amortise the ring fill (measured
-    // on 512x512x2048: 32 -> 5.08 ms, 128 -> 4.56 ms, 512 -> 4.43 ms)
-    const int64_t ychunk = 512;
-    const int32_t ztiles = (d.cols + 63) / 64;
-    const int64_t chunks = (ny + ychunk - 1) / ychunk;
-    const int64_t blocks = ychunk > 0 ? chunks * d.rows * ztiles : kMaxI32;
-    const double band4 = 63.0 * std::fabs(a.uz) + (4 * 4 + 4) * std::fabs(a.uy) + 4.0;
-    const double band1 = 63.0 * std::fabs(a.uz) + (kAffAhead + 1) * std::fabs(a.uy) + 4.0;
-    // the ring kernels take floors of u as ints: every u of the grid
-    // (u0 + y uy - z uz over the whole output) must stay within +-1e9
+    // The strip kernel takes floors of u as ints: every u of the grid
+    // (u0 + y uy - z uz over the whole output) must stay within +-1e9.
     const double ue[4] = {a.u0, a.u0 + (double)(ny - 1) * a.uy, a.u0 - (double)(d.cols - 1) * a.uz,
                           a.u0 + (double)(ny - 1) * a.uy - (double)(d.cols - 1) * a.uz};
     bool u_ok = true;
     for (double v : ue) u_ok = u_ok && std::fabs(v) < 1.0e9;
-    if (u_ok && blocks < kMaxI32 && std::fabs(a.uy) <= 0.499 && band4 <= 32.0) {
-        if (d.cols % 4 == 0 && ((uintptr_t)vol & 15) == 0 && ((uintptr_t)in & 3) == 0 &&
-            ny < (int64_t(1) << 30)) {
-            // row kernel: persistent, kAffRows-row strips; when the strips
-            // do not fill the resident wavefronts, the y range is split in
-            // multiples of kAffRestart
-            const int64_t strips = ((int64_t)d.rows + kAffRows - 1) / kAffRows * ztiles;
-            const int64_t resident = (int64_t)kAffRowsPerCU * device_cus();
-            const int64_t ychunks = (ny + kAffRestart - 1) / kAffRestart;
-            int64_t split = strips >= resident ? 1 : (resident + strips - 1) / strips;
-            split = split < ychunks ? split : ychunks;
-            const int64_t ylen = (ychunks + split - 1) / split * kAffRestart;
-            const int64_t items = strips * ((ny + ylen - 1) / ylen);
-            const int64_t grid = items < resident ? items : resident;
-            const RowsArgs ra{a, ylen, strips, items, ztiles};
-            hipLaunchKernelGGL(k_affine_rows, dim3((unsigned)grid), dim3(64), 0, stream, ra);
+    // The images a chunk adds fit the loads of one chunk and its band the
+    // ring (2 images besides the span, one for rounding).
+    auto fits = [&](bool phase) {
+        return kChunk * std::fabs(a.uy) + 1.0 <= kNewImages &&
+               (strip_window(phase) - 1) * std::fabs(a.uz) + kChunk * std::fabs(a.uy) + 3.0 <=
+                   kRing;
+    };
+    // Outputs the last-level cache holds: it joins partial lines, and plain
+    // stores let it (28x667x135, 74 MB: 35 us with whole lines streamed past
+    // it, 22 so).  Larger ones are streamed in whole lines.
+    const bool small = 4 * ny * d.rows * (int64_t)d.cols <= kCachedBytes;
+    const bool lines = ((uintptr_t)vol & 127) == 0 && d.cols % 32 == 0;
+    const bool phase = !small && !lines && fits(true);
+    if (u_ok && fits(phase) && d.cols >= 2 && ny < (int64_t(1) << 30) && ((uintptr_t)in & 1) == 0 &&
+        ((uintptr_t)vol & 3) == 0) {
+        int s = 1;   // rows s apart start at one place of a 128-byte line
+        while (phase && (int64_t)s * d.cols % 32 != 0) s *= 2;
+        const int64_t plane_px = (int64_t)d.rows * d.cols;
+        const int32_t ztiles = (d.cols + (phase ? 31 : 0) + kStripCols - 1) / kStripCols;
+        const int64_t per_class = ((int64_t)d.rows + s - 1) / s;
+        const int64_t strips = s * ((per_class + kStripRows - 1) / kStripRows) * ztiles;
+        const int64_t ylen = strip_ylen(strips, ny, strip_wg_per_cu(phase),
+                                        2 * (int64_t)d.planes * plane_px);
+        const int64_t blocks = strips * ((ny + ylen - 1) / ylen);
+        if (blocks < kMaxI32) {
+            const StripArgs sa{a, ylen, strips, ztiles, s};
+            auto go = [&](auto kern) {
+                hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kStripBlock), 0, stream, sa);
+            };
+            if (phase)
+                go(k_affine_strip<true, true>);
+            else if (lines && !small)
+                go(k_affine_strip<false, true>);
+            else
+                go(k_affine_strip<false, false>);
             return hip_status(hipGetLastError());
         }
-        const RingArgs<uint16_t> ra{a, ychunk, ztiles};
-        hipLaunchKernelGGL((k_affine_ring<uint16_t, 4, 4>), dim3((unsigned)blocks), dim3(64), 0,
-                           stream, ra);
-        return hip_status(hipGetLastError());
-    }
-    if (u_ok && blocks < kMaxI32 && std::fabs(a.uy) <= 0.999 && band1 <= 32.0) {
-        const RingArgs<uint16_t> ra{a, ychunk, ztiles};
-        hipLaunchKernelGGL((k_affine_ring<uint16_t, 1, kAffAhead>), dim3((unsigned)blocks),
-                           dim3(64), 0, stream, ra);
-        return hip_status(hipGetLastError());
     }
     const bool vec = d.cols % 4 == 0 && ((uintptr_t)vol & 15) == 0;
     if (vec)
