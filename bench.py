@@ -391,27 +391,32 @@ def bench_rolling(torch, dsk, synth):
                                  {"shift_px": (3652 - 87) / 49}),
                                 ("stack_512x512x2048", (N, R, C),
                                  {"angle_deg": ANGLE, "step_um": STEP, "pixel_um": PIXEL})):
-        st = synth.blob_stack((n, r, c), 50, 21, device="cuda")
+        # two scans in turn: every image differs from the one it replaces
+        sts = [synth.blob_stack((n, r, c), 50, 21 + i, device="cuda") for i in range(2)]
+        st = sts[0]
         rv = RollingView(n, r, c, **kw)
         for i in range(n):
             rv.update(i, st[i])
         torch.cuda.synchronize()
-        k = [0]
+        k = [n]
 
         def one():
-            rv.update(k[0] % n, st[k[0] % n])
+            rv.update(k[0] % n, sts[k[0] // n % 2][k[0] % n])
             k[0] += 1
         ms = _median_ms(torch, one, 50)          # one call, host launch included
         kms = _b2b_ms(torch, one, 100)           # calls back to back
-        # bytes per update: the image, the leaf read and written, the FP64
-        # running sum read and written, both projections written, and per
-        # tree level a sibling read and the parent written
+        # bytes per update: the image; over the columns it reaches the leaf
+        # read and written, the FP64 running sum read and written, both
+        # projections written, and per tree level a sibling read and the
+        # parent written; over the padding the leaf, the sum and the root
+        # read and both projections written
         levels = max(1, math.ceil(math.log2(n))) if n > 1 else 0
         w = rv.width
-        alg = 2 * r * c + (8 + 16 + 8 + 8 * levels) * r * w
+        band = min(w, c + 1)
+        alg = 2 * r * c + (8 + 16 + 8 + 8 * levels) * r * band + 24 * r * (w - band)
         res[name] = {"ms_per_image": ms, "images_per_s": 1e3 / ms, "width": w,
                      "kernel_ms": kms, "algorithmic_bytes": alg, "gbs": alg / kms / 1e6}
-        del rv, st
+        del rv, st, sts
         torch.cuda.empty_cache()
     return res
 
