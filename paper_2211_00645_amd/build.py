@@ -27,7 +27,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libdeskew.so")
 LIB_ASAN = os.path.join(PKG, "libdeskew_asan.so")
 LIB_BOUNDS = os.path.join(PKG, "libdeskew_bounds.so")
-SOURCES = ["deskew.hip", "batch.hip", "tune.hip", "rolling.hip", "view.hip", "affine.hip"]
+SOURCES = ["deskew.hip", "split.hip", "batch.hip", "tune.hip", "rolling.hip", "view.hip", "affine.hip"]
 ARCH = os.environ.get("DSK_OFFLOAD_ARCH", "gfx950")
 FLAGS = [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
          "-ffp-contract=off",

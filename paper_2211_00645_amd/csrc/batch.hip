@@ -248,12 +248,12 @@ int time_shape(dsk_batch *bt, const dsk_tune &t, hipStream_t s, int reps, double
 int launch_per_job(const dsk_batch *bt, bool tuned, hipStream_t s) {
     for (size_t i = 0; i < bt->jobs.size(); ++i) {
         const dsk_job &j = bt->jobs[i];
-        const dsk_tune t = tuned ? bt->job_tunes[i]
-                                 : default_tune(j.in, 0, j.dims,
-                                                (int64_t)j.dims.rows * j.dims.cols, j.vol,
-                                                j.out_width);
-        const int st = launch_forward(j.in, 0, j.dims, j.offsets_dev, j.shift_px, j.origin, j.vol,
-                                      j.psum, j.pmax, j.out_width, t, s);
+        const int st =
+            tuned ? launch_forward(j.in, 0, j.dims, j.offsets_dev, j.shift_px, j.origin, j.vol,
+                                   j.psum, j.pmax, j.out_width, bt->job_tunes[i], s)
+                  : launch_forward_default(j.in, 0, j.dims, dense_layout(j.dims), j.offsets_dev,
+                                           j.shift_px, j.origin, j.vol, j.psum, j.pmax,
+                                           j.out_width, s);
         if (st != DSK_OK) return st;
     }
     return DSK_OK;

@@ -153,13 +153,20 @@ inline InLayout dense_layout(dsk_dims d) {
 }
 
 #if defined(DSK_CHECK_BOUNDS) && DSK_CHECK_BOUNDS
-// Bounds-violation count of the batch kernels' translation unit (batch.hip).
+// Bounds-violation counts of the other translation units with checked kernels.
 int batch_bounds_violations(unsigned long long *count, bool reset);
+int split_bounds_violations(unsigned long long *count, bool reset);
 #endif
 
-// The launch shape of a frame when the caller gives none (deskew.hip).
-dsk_tune default_tune(const void *in, int in_is_f32, dsk_dims d, int64_t in_plane,
-                      const float *vol, int64_t width);
+// The same without a launch shape: the library's choice for the frame.
+int launch_forward_default(const void *in, int in_is_f32, dsk_dims d, const InLayout &lay,
+                           const double *offs, double shift, int64_t origin, float *vol,
+                           float *psum, float *pmax, int64_t width, hipStream_t stream);
+
+// The split kernel's launch (split.hip): a frame's tiles (per row) on checked
+// arguments.
+hipError_t launch_split(const FwdArgs<uint16_t> &a, int64_t tiles, hipStream_t s);
+hipError_t launch_split(const FwdArgs<float> &a, int64_t tiles, hipStream_t s);
 
 // Launchers (deskew.hip) used by the other translation units.
 int launch_forward(const void *in, int in_is_f32, dsk_dims d, const double *offs,

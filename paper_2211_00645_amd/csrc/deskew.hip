@@ -18,11 +18,12 @@ extern "C" int dsk_debug_bounds_violations(unsigned long long *count, int reset)
     if (!count) return DSK_EINVAL;
     *count = 0;
 #if DSK_CHECK_BOUNDS
-    unsigned long long a = 0, b = 0;
+    unsigned long long a = 0, b = 0, c = 0;
     if (dsk::read_bounds_violations(&a, reset != 0) != 0 ||
-        dsk::batch_bounds_violations(&b, reset != 0) != 0)
+        dsk::batch_bounds_violations(&b, reset != 0) != 0 ||
+        dsk::split_bounds_violations(&c, reset != 0) != 0)
         return DSK_EHIP;
-    *count = a + b;
+    *count = a + b + c;
     return 1;
 #else
     (void)reset;
@@ -246,23 +247,30 @@ static bool tiles_aligned(const float *vol, dsk_dims d, int64_t width, const dsk
 //    against 4971), and more planes need the pacing (256x256x512, 392 MB:
 //    4441 against 3809);
 //  * with few wavefronts a compute unit a 4-plane pipeline keeps enough
-//    loads in flight: 256x256x512 (5 wavefronts) 4409 -> 5140, 256x128x1024
-//    (3.5) 3369 -> 4426; from 7 on the two are equal, from 14 on 2 planes
+//    loads in flight: 256x256x512 (5 wavefronts) 4409 -> 5140, 128x320x512
+//    (5) 45.4 -> 39.8 us; from 7 on the two are equal, from 14 on 2 planes
 //    do better.
 constexpr int kPartialLinePace = 5100;
 constexpr int64_t kSmallBytes = 450000000;
 constexpr int32_t kSmallPlanes = 100;
 constexpr int64_t kFewTilesPerCU = 6;
+//  * without a volume, stacks of up to kSmallProjBytes do better unpaced, in
+//    us: 300x400x1024 uint16 (246 MB) 69.5 against 74.0, 128x512x2000 (262 MB)
+//    63.0 against 66.3; 256x512x1600 (419 MB) 111 against 106 paced
+constexpr int64_t kSmallProjBytes = 300000000;
 
-dsk_tune default_tune(const void *in, int in_is_f32, dsk_dims d, int64_t in_plane,
+static dsk_tune default_tune(const void *in, int in_is_f32, dsk_dims d, int64_t in_plane,
                       const float *vol, int64_t width) {
-    if (!vol) return kDefaultProjTune;
+    const int64_t stack_bytes = (int64_t)d.planes * d.rows * d.cols * (in_is_f32 ? 4 : 2);
+    if (!vol) {
+        dsk_tune t = kDefaultProjTune;
+        if (stack_bytes <= kSmallProjBytes) t.pace_gbs = 0;
+        return t;
+    }
     dsk_tune t = kDefaultTune;
-    if (!in || !dims_ok(d) || check_frame(d, 0, width) != DSK_OK) return t;   // refused later
     const int vec = vec_mode(t, d, width, in, in_is_f32, vol, in_plane);
     if (vec == VEC_NONE) return t;
-    const int64_t bytes =
-        (int64_t)d.planes * d.rows * ((in_is_f32 ? 4 : 2) * (int64_t)d.cols + 4 * width);
+    const int64_t bytes = stack_bytes + 4 * (int64_t)d.planes * d.rows * width;
     const bool aligned = tiles_aligned(vol, d, width, t, vec);
     if (bytes <= kSmallBytes && d.planes <= kSmallPlanes) {
         if (aligned || in_is_f32) t.pace_gbs = 0;
@@ -273,20 +281,67 @@ dsk_tune default_tune(const void *in, int in_is_f32, dsk_dims d, int64_t in_plan
     return t;
 }
 
-int launch_forward_layout(const void *in, int in_is_f32, dsk_dims d, const InLayout &lay,
-                          const double *offs, double shift, int64_t origin, float *vol,
-                          float *psum, float *pmax, int64_t width, const dsk_tune &t,
-                          hipStream_t stream) {
+// Checks of a forward call; every row must lie inside the readable extent.
+static int check_forward(const void *in, dsk_dims d, const InLayout &lay, const double *offs,
+                         double shift, int64_t origin, const float *vol, const float *psum,
+                         const float *pmax, int64_t width) {
     if (!in || !dims_ok(d) || (!vol && !psum && !pmax)) return DSK_EINVAL;
     if (!offs && !std::isfinite(shift)) return DSK_EINVAL;
-    if (!tune_ok(t)) return DSK_EINVAL;
-    int st = check_frame(d, origin, width);
+    const int st = check_frame(d, origin, width);
     if (st != DSK_OK) return st;
-    // every row must lie inside the readable extent
     const int64_t last = (int64_t)(d.planes - 1) * lay.plane + (int64_t)(d.rows - 1) * lay.row;
     if (lay.row < d.cols || lay.plane < (int64_t)(d.rows - 1) * lay.row + d.cols || lay.lo < 0 ||
         lay.hi < last + d.cols)
         return DSK_ESHAPE;
+    return DSK_OK;
+}
+
+// Tiles per compute unit up to which a frame goes to the split kernel, in
+// quarters.  us, k_forward_vec in its best shape -> split:
+//   volume and projections: 64x128x256 uint16 (1 tile) 14.8 -> 10.2,
+//     302x64x128 (1.25) 69 -> 42, 128x128x512 (2) 30.7 -> 21.4; 40x400x500
+//     (4.7) 14.8 -> 18.1, 256x256x512 (5) 76 -> 103
+//   volume alone (no sums, so no LDS and no barriers): 37x131x517 (1.5)
+//     11.2 -> 9.5, 128x256x512 (4) 35.6 -> 26.6; 200x512x512 (8) 89 -> 142
+//   projections alone: 64x128x256 15.8 -> 8.7, 302x64x128 28 -> 19,
+//     64x256x512 (3) 16.7 -> 12.7; 128x320x512 (5) 30.7 -> 32.1
+constexpr int64_t kSplitVolume = 10, kSplitVolumeAlone = 24, kSplitProjections = 12;
+
+int launch_forward_default(const void *in, int in_is_f32, dsk_dims d, const InLayout &lay,
+                           const double *offs, double shift, int64_t origin, float *vol,
+                           float *psum, float *pmax, int64_t width, hipStream_t stream) {
+    const int st = check_forward(in, d, lay, offs, shift, origin, vol, psum, pmax, width);
+    if (st != DSK_OK) return st;
+    // the split kernel's tile is the general vector tile: 64 groups
+    const int64_t tiles = (width + 255) / 256;
+    const uintptr_t im = in_is_f32 ? 3 : 1;
+    const int64_t quarters = !vol ? kSplitProjections
+                                  : (psum || pmax ? kSplitVolume : kSplitVolumeAlone);
+    if (width >= 4 &&
+        vec_mode(kDefaultTune, d, width, in, in_is_f32, vol, lay.plane) != VEC_NONE &&
+        ((uintptr_t)in & im) == 0 && ((uintptr_t)vol & 3) == 0 &&
+        4 * tiles * d.rows <= quarters * device_cus()) {
+        auto go = [&](auto *p) {
+            using TIn = std::remove_const_t<std::remove_pointer_t<decltype(p)>>;
+            const FwdArgs<TIn> a{p, vol, psum, pmax, offs, shift, (double)origin, width,
+                                 d.planes, d.rows, d.cols, lay.row, lay.plane, lay.lo, lay.hi,
+                                 0u, 0u, 0, 0, (int64_t)d.rows * width, 0};
+            return hip_status(launch_split(a, tiles, stream));
+        };
+        return in_is_f32 ? go((const float *)in) : go((const uint16_t *)in);
+    }
+    return launch_forward_layout(in, in_is_f32, d, lay, offs, shift, origin, vol, psum, pmax,
+                                 width, default_tune(in, in_is_f32, d, lay.plane, vol, width),
+                                 stream);
+}
+
+int launch_forward_layout(const void *in, int in_is_f32, dsk_dims d, const InLayout &lay,
+                          const double *offs, double shift, int64_t origin, float *vol,
+                          float *psum, float *pmax, int64_t width, const dsk_tune &t,
+                          hipStream_t stream) {
+    if (!tune_ok(t)) return DSK_EINVAL;
+    const int st = check_forward(in, d, lay, offs, shift, origin, vol, psum, pmax, width);
+    if (st != DSK_OK) return st;
     const int vec = vec_mode(t, d, width, in, in_is_f32, vol, lay.plane);
     const bool align = tiles_aligned(vol, d, width, t, vec);
     const int64_t tiles = tiles_x(width, t, vec);
@@ -328,8 +383,8 @@ extern "C" int dsk_deskew_u16(const uint16_t *in, dsk_dims d, dsk_geom g, float 
     st = dsk_plan(d, nullptr, s, &w, &b);
     if (st != DSK_OK) return st;
     if (out_width > 0) w = out_width;
-    return launch_forward(in, 0, d, nullptr, s, b, vol, psum, pmax, w,
-                          default_tune(in, 0, d, (int64_t)d.rows * d.cols, vol, w), stream);
+    return launch_forward_default(in, 0, d, dense_layout(d), nullptr, s, b, vol, psum, pmax, w,
+                                  stream);
 }
 
 extern "C" int dsk_deskew_channel_u16(const uint16_t *frames, int64_t frame_cols, int64_t col0,
@@ -347,26 +402,26 @@ extern "C" int dsk_deskew_channel_u16(const uint16_t *frames, int64_t frame_cols
     if (out_width > 0) w = out_width;
     const int64_t plane = (int64_t)d.rows * frame_cols;
     const InLayout lay{frame_cols, plane, col0, (int64_t)d.planes * plane - col0};
-    return launch_forward_layout(frames + col0, 0, d, lay, nullptr, s, b, vol, psum, pmax, w,
-                                 default_tune(frames + col0, 0, d, plane, vol, w), stream);
+    return launch_forward_default(frames + col0, 0, d, lay, nullptr, s, b, vol, psum, pmax, w,
+                                  stream);
 }
 
 extern "C" int dsk_deskew_offsets_u16(const uint16_t *in, dsk_dims d, const double *offsets_dev,
                                       int64_t origin, float *vol, float *psum, float *pmax,
                                       int64_t out_width, hipStream_t stream) {
     if (!offsets_dev || out_width <= 0) return DSK_EINVAL;
-    return launch_forward(in, 0, d, offsets_dev, 0.0, origin, vol, psum, pmax, out_width,
-                          default_tune(in, 0, d, (int64_t)d.rows * d.cols, vol, out_width),
-                          stream);
+    if (!dims_ok(d)) return DSK_EINVAL;
+    return launch_forward_default(in, 0, d, dense_layout(d), offsets_dev, 0.0, origin, vol, psum,
+                                  pmax, out_width, stream);
 }
 
 extern "C" int dsk_deskew_offsets_f32(const float *in, dsk_dims d, const double *offsets_dev,
                                       int64_t origin, float *vol, float *psum, float *pmax,
                                       int64_t out_width, hipStream_t stream) {
     if (!offsets_dev || out_width <= 0) return DSK_EINVAL;
-    return launch_forward(in, 1, d, offsets_dev, 0.0, origin, vol, psum, pmax, out_width,
-                          default_tune(in, 1, d, (int64_t)d.rows * d.cols, vol, out_width),
-                          stream);
+    if (!dims_ok(d)) return DSK_EINVAL;
+    return launch_forward_default(in, 1, d, dense_layout(d), offsets_dev, 0.0, origin, vol, psum,
+                                  pmax, out_width, stream);
 }
 
 extern "C" int dsk_deskew_offsets_tuned(const void *in, int in_is_f32, dsk_dims d,
@@ -375,9 +430,11 @@ extern "C" int dsk_deskew_offsets_tuned(const void *in, int in_is_f32, dsk_dims 
                                         int64_t out_width, const dsk_tune *tune,
                                         hipStream_t stream) {
     if (out_width <= 0) return DSK_EINVAL;
-    const dsk_tune t = tune ? *tune
-                            : default_tune(in, in_is_f32, d, (int64_t)d.rows * d.cols, vol,
-                                           out_width);
+    if (!dims_ok(d)) return DSK_EINVAL;
+    if (!tune)
+        return launch_forward_default(in, in_is_f32 ? 1 : 0, d, dense_layout(d), offsets_dev,
+                                      shift_px, origin, vol, psum, pmax, out_width, stream);
+    const dsk_tune &t = *tune;
     return launch_forward(in, in_is_f32 ? 1 : 0, d, offsets_dev, shift_px, origin, vol, psum,
                           pmax, out_width, t, stream);
 }

@@ -309,6 +309,14 @@ struct RawWin<uint16_t> {
         e1 = q[1];
         e2 = q[2];
     }
+    // from any element
+    __device__ __forceinline__ void load_any(const uint16_t *p) {
+        typedef uint32_t u32x3_any __attribute__((ext_vector_type(3), aligned(2)));
+        const u32x3_any q = *(const u32x3_any *)p;
+        e0 = q.x;
+        e1 = q.y;
+        e2 = q.z;
+    }
     // Wait for the load here (an empty asm that reads the registers), so no
     // load is pending across a loop back-edge: the wait counter is in-order
     // and shared with stores, and a pending load there would make the
@@ -327,6 +335,15 @@ struct RawWin<uint16_t> {
         v[3] = (float)(a1 >> 16);
         v[4] = (float)(a2 & 0xffffu);
     }
+    // every element of the window
+    __device__ __forceinline__ void all(float v[6]) const {
+        v[0] = (float)(e0 & 0xffffu);
+        v[1] = (float)(e0 >> 16);
+        v[2] = (float)(e1 & 0xffffu);
+        v[3] = (float)(e1 >> 16);
+        v[4] = (float)(e2 & 0xffffu);
+        v[5] = (float)(e2 >> 16);
+    }
 };
 
 template <>
@@ -339,6 +356,7 @@ struct RawWin<float> {
         __builtin_memcpy(&a, p, sizeof(a));   // 4-byte aligned
         b = p[4];
     }
+    __device__ __forceinline__ void load_any(const float *p) { load(p); }
     __device__ __forceinline__ void settle() const {
         asm volatile("" ::"v"(a.x), "v"(a.y), "v"(a.z), "v"(a.w), "v"(b));
     }
@@ -349,6 +367,7 @@ struct RawWin<float> {
         v[3] = a.w;
         v[4] = b;
     }
+    __device__ __forceinline__ void all(float v[5]) const { extract(0, v); }
 };
 
 // Column layout of output row r for the vector kernel.  The flat volume
@@ -420,7 +439,10 @@ __device__ __forceinline__ int edge_col(const RowGeo &g, int W, int j) {
 // columns; volume stores are 16 bytes at any 4-byte boundary; and a 16-bit
 // window's parity is a plane's (an odd plane pitch) and a lane's own (the
 // moved group) instead of the launch's.
-template <typename TIn, int BLOCK, int G, int UNR, bool NT, bool VOL, bool GEN>
+//
+// ACC: the tile keeps the sums and maxima (the split kernel takes them from
+// LDS instead).
+template <typename TIn, int BLOCK, int G, int UNR, bool NT, bool VOL, bool GEN, bool ACC = true>
 struct VecTile {
     enum { OUT = 0, IN = 1, MIXED = 2 };
     using Win = RawWin<TIn>;
@@ -448,15 +470,16 @@ struct VecTile {
     int ls0, lwin;
     float lwlo, lwhi;
 
-    __device__ __forceinline__ VecTile(const FwdArgs<TIn> &args, int row, int tile)
+    // tid: this thread's place in the tile's BLOCK threads
+    __device__ __forceinline__ VecTile(const FwdArgs<TIn> &args, int row, int tile, int tid)
         : a(args), r(row), W((int)args.W), C(args.C), N(args.N) {
         const RowGeo rg = GEN ? RowGeo{0, (W + 3) / 4} : row_geo(r, W);
         ca = rg.ca;
         ng = rg.ng;
         rstep = a.in_plane;
         ostep = a.vol_plane;
-        wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-        lane = (int)threadIdx.x & 63;
+        wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+        lane = tid & 63;
         int base = tile * BLOCK * G;
         if constexpr (VOL && !GEN) {
             // shift the row's tile grid back by the groups that lie between
@@ -504,7 +527,7 @@ struct VecTile {
                 // lanes before the row's first group (an aligned tile grid)
                 // repeat it, as lanes past the last repeat the last
                 const int w0 = base + 64 * wv + BLOCK * g;
-                gx[g] = 4 * max(0, min(base + (int)threadIdx.x + BLOCK * g, ng - 1));
+                gx[g] = 4 * max(0, min(base + tid + BLOCK * g, ng - 1));
                 pfirst[g] = 4 * max(0, min(w0, ng - 1));
                 plast[g] = 4 * max(0, min(w0 + 63, ng - 1));
             } else {
@@ -592,8 +615,10 @@ struct VecTile {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             d[i] = fmaf(whi, v[i + 1], wlo * v[i]);
-            acc[g][i] += (double)d[i];
-            mx[g][i] = fmaxf(mx[g][i], d[i]);
+            if constexpr (ACC) {
+                acc[g][i] += (double)d[i];
+                mx[g][i] = fmaxf(mx[g][i], d[i]);
+            }
         }
     }
 
@@ -678,6 +703,54 @@ struct VecTile {
                 vv[i] = load_px(bounded(rp, C, a.in - a.in_lo, a.in + a.in_hi), p + i, C);
         }
         interp(g, vv, wlo, whi, d);
+    }
+
+    // ---- split kernel (one group per lane) ----------------------------------
+
+    __device__ __forceinline__ void load_at(const TIn *rp, int off, Win &w) const {
+        w.load_any(bounded(rp + off, Win::kLen, a.in - a.in_lo, a.in + a.in_hi));
+    }
+
+    // Window start of group 0 in plane n (v its packed start/shift), clamped
+    // to the row's neighbourhood and, in a plane whose row lies at a stack
+    // end, to the readable extent (at any element there: an aligned window
+    // may not reach the extent's last one).
+    __device__ __forceinline__ int exact_off(int n, int v) const {
+        int lo = lo_of(v), hi = hi_of(v);
+        if (n == first_special || n == last_special) {
+            const int64_t grow = (int64_t)r * a.in_row + (int64_t)n * rstep;
+            const int64_t lo_ok = -grow - a.in_lo, hi_ok = a.in_hi - Win::kLen - grow;
+            lo = (int)(lo_ok > (int64_t)lo ? lo_ok : (int64_t)lo);
+            hi = (int)(hi_ok < (int64_t)hi ? hi_ok : (int64_t)hi);
+        }
+        const int off = first_px(0, v) - win_shift(0, v);
+        return off < lo ? lo : (off > hi ? hi : off);
+    }
+
+    // Interpolate group 0 of plane n from its window at exact_off(n, v).
+    // Pixels outside the row are masked, and every pixel inside it lies in the
+    // window wherever the readable extent moved that to; only planes at a
+    // stack end have moved windows with pixels inside.
+    __device__ __forceinline__ void compute_exact(int n, const Win &w, int v, float wlo, float whi,
+                                                  float d[4]) {
+        float vv[5];
+        const int p = first_px(0, v);
+        w.extract(win_shift(0, v), vv);
+        if (n == first_special || n == last_special) {
+            float e[Win::kLen];
+            w.all(e);
+            const int at = p - exact_off(n, v);   // first needed pixel's place
+#pragma unroll
+            for (int i = 0; i < 5; ++i) {
+                vv[i] = e[0];
+#pragma unroll
+                for (int k = 1; k < Win::kLen; ++k) vv[i] = at + i == k ? e[k] : vv[i];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 5; ++i)
+            if ((unsigned)(p + i) >= (unsigned)C) vv[i] = 0.0f;
+        interp(0, vv, wlo, whi, d);
     }
 
     // ---- with a volume ---------------------------------------------------
@@ -1118,7 +1191,7 @@ __device__ __forceinline__ void fwd_vec_block(const FwdArgs<TIn> &a, int tiles_x
             r = (int)(b - (int64_t)k * a.R);
             xt = middle_out(k, tiles_x);
         }
-        VecTile<TIn, BLOCK, G, UNR, NT, VOL, GEN> vt(a, r, xt);
+        VecTile<TIn, BLOCK, G, UNR, NT, VOL, GEN> vt(a, r, xt, (int)threadIdx.x);
         vt.run();
     }
 }
@@ -1148,6 +1221,128 @@ __global__ __launch_bounds__(BLOCK, vec_waves_per_eu(G, UNR, VOL, (int)sizeof(TI
     const int64_t eb = a.edge_wg, d = blockIdx.x;
     const int64_t lb = (VOL && d >= eb) ? eb + xcd_remap(d - eb, (int64_t)gridDim.x - eb) : d;
     fwd_vec_block<TIn, BLOCK, G, UNR, NT, VOL, GEN>(a, tiles_x, lb);
+}
+
+// Split kernel: frames of few tiles.  A wavefront of k_forward_vec walks a
+// tile's planes one load latency after another, and with a tile or two per
+// SIMD nothing hides it (302x64x128 into 1221 columns: 1.4 TB/s).  Here the 4
+// wavefronts of a workgroup share one tile of 64 groups: wavefront w takes
+// planes w U .. w U + U - 1 of every step of 4 U planes, the loads of the next
+// step in flight while one is computed, and leaves the deskewed values in LDS
+// (two buffers, one barrier a step); thread t then adds the step's planes, in
+// plane order, to column t's sum and maximum, so the result is bitwise that of
+// every other path.  The tile is the general one (any alignment).
+constexpr int kSplitWaves = 4;
+constexpr int kSplitBlock = 64 * kSplitWaves;
+
+template <typename TIn, int U, bool VOL>
+__global__ __launch_bounds__(kSplitBlock) void k_forward_split(FwdArgs<TIn> a, int tiles_x) {
+    using Tile = VecTile<TIn, 64, 1, U, false, VOL, true, false>;
+    using Win = typename Tile::Win;
+    using Chunk = typename Tile::Chunk;
+    constexpr int kStep = U * kSplitWaves;
+    __shared__ __align__(16) float lds[2][kStep][256];
+    const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
+    const int r = (int)(b / tiles_x), xt = (int)(b - (int64_t)r * tiles_x);
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    Tile vt(a, r, xt, lane);
+    const int N = a.N;
+    const bool proj = a.psum || a.pmax;
+    // planes to walk: with a volume all of them, without one those that
+    // reach the tile's columns
+    int n_lo = 0, n_hi = N;
+    Chunk cur, nxt;
+    if constexpr (!VOL) {
+        n_lo = N;
+        n_hi = 0;
+        for (int c0 = 0; c0 < N; c0 += 64) {
+            vt.load_chunk(c0, cur);
+            const uint64_t act = (N - c0 >= 64 ? ~0ull : ((1ull << (N - c0)) - 1)) & ~cur.bout;
+            if (act) {
+                n_lo = min(n_lo, c0 + (int)__builtin_ctzll(act));
+                n_hi = max(n_hi, c0 + 64 - (int)__builtin_clzll(act));
+            }
+        }
+    }
+    double acc = 0.0;
+    float mx = -__builtin_huge_valf();
+    // planes outside the range are zero at every column
+    if (n_lo > 0 || n_hi < N) mx = 0.0f;
+    const int first = n_lo / kStep * kStep;
+
+    // Every step issues U window loads and U stores with no branch around
+    // them (planes past the last repeat it, planes that miss the tile read
+    // the row's ends), so the waits for the loads leave the stores in flight.
+    Win win[U], nwin[U];
+    auto issue = [&](int n0, Win v[U]) {
+        const int cw = n0 >= cur.c0 + 64 ? nxt.win : cur.win;
+        const int c0 = n0 >= cur.c0 + 64 ? nxt.c0 : cur.c0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int n = min(n0 + u, N - 1);
+            const int vv = __builtin_amdgcn_readlane(cw, n - c0);
+            vt.load_at(vt.rp0 + (int64_t)n * vt.rstep, vt.exact_off(n, vv), v[u]);
+        }
+    };
+    if (first < n_hi) {
+        vt.load_chunk(first & ~63, cur);
+        nxt = cur;
+        if (cur.c0 + 64 < N) vt.load_chunk(cur.c0 + 64, nxt);
+        issue(min(first + w * U, N - 1), win);
+    }
+    int buf = 0;
+    for (int s0 = first; s0 < n_hi; s0 += kStep, buf ^= 1) {
+        // a step lies in one chunk (64 is a multiple of it)
+        issue(min(s0 + kStep + w * U, N - 1), nwin);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int n = min(s0 + w * U + u, N - 1), li = n - cur.c0;
+            const int vv = __builtin_amdgcn_readlane(cur.win, li);
+            float d[4];
+            vt.compute_exact(n, win[u], vv, vt.lane_f(cur.wlo, li), vt.lane_f(cur.whi, li), d);
+            if constexpr (VOL) vt.store(0, vt.op0 + (int64_t)n * vt.ostep, d);
+            if (proj) *(f32x4 *)&lds[buf][w * U + u][4 * lane] = f32x4{d[0], d[1], d[2], d[3]};
+        }
+        if (proj) {
+            __syncthreads();
+            float d[kStep];
+#pragma unroll
+            for (int j = 0; j < kStep; ++j) d[j] = lds[buf][j][tid];
+            if (N - s0 >= kStep) {
+#pragma unroll
+                for (int j = 0; j < kStep; ++j) {
+                    acc += (double)d[j];
+                    mx = fmaxf(mx, d[j]);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < kStep; ++j) {
+                    if (j < N - s0) {
+                        acc += (double)d[j];
+                        mx = fmaxf(mx, d[j]);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            nwin[u].settle();
+            win[u] = nwin[u];
+        }
+        if (s0 + kStep >= cur.c0 + 64) {
+            cur = nxt;
+            if (cur.c0 + 64 < N) vt.load_chunk(cur.c0 + 64, nxt);
+        }
+    }
+    if (proj) {
+        // thread t: column t mod 4 of group t / 4
+        const int g = min(xt * 64 + (tid >> 2), (vt.W + 3) / 4 - 1);
+        const int x = min(4 * g, vt.W - 4) + (tid & 3);
+        const int64_t o = (int64_t)r * vt.W + x, rw = (int64_t)a.R * vt.W;
+        if (a.psum) *bounded(a.psum + o, 1, a.psum, a.psum + rw) = (float)acc;
+        if (a.pmax) *bounded(a.pmax + o, 1, a.pmax, a.pmax + rw) = mx;
+    }
 }
 
 // Job record of the persistent ragged-batch kernel (device-resident table).
