@@ -443,7 +443,8 @@ extern "C" int dsk_deskew_offsets_tuned(const void *in, int in_is_f32, dsk_dims 
 
 namespace {
 
-constexpr int kBwdBlock = 256;
+constexpr int kBwdBlock = 256, kBwdWide = 1024;
+constexpr int64_t kBwdWidePerCU = 8;
 
 // Rows per backward workgroup: about 8192 raw columns per workgroup.
 int bwd_rows_per_block(dsk_dims d) {
@@ -476,24 +477,30 @@ int launch_backward(const float *in, const float *gvol, dsk_dims d, const double
     if (goff && ws_bytes < dsk_shear_grad_workspace_bytes(d)) return DSK_ESHAPE;
     BwdArgs a{in, gvol, gin, (double *)ws, offs, 0.0, (double)origin, width,
               d.planes, d.rows, d.cols, bwd_rows_per_block(d), G};
-    const dim3 grid((unsigned)blocks), block(kBwdBlock);
-    // 4 columns per thread when the rows of the stack and of the adjoint
-    // start 16-byte aligned
-    const bool vec = d.cols % 4 == 0 && (!goff || ((uintptr_t)in & 15) == 0) &&
-                     (!gin || ((uintptr_t)gin & 15) == 0) && ((uintptr_t)gvol & 3) == 0;
-    auto go = [&](auto V) {
+    const dim3 grid((unsigned)blocks);
+    // 4 columns per thread where rows have them and the buffers their
+    // elements' alignment
+    const bool vec = d.cols >= 4 && (!goff || ((uintptr_t)in & 3) == 0) &&
+                     (!gin || ((uintptr_t)gin & 3) == 0) && ((uintptr_t)gvol & 3) == 0;
+    // A workgroup has about 2048 groups of 4 columns: 256 threads take 8 each;
+    // with fewer than kBwdWidePerCU workgroups per compute unit 1024 threads
+    // take 2 (37x131x517, 333 workgroups: 28.8 -> 8.6 us).
+    auto go = [&](auto B, auto V) {
+        constexpr int n = decltype(B)::value;
         constexpr bool v = decltype(V)::value;
         if (gin && goff)
-            hipLaunchKernelGGL((k_backward<kBwdBlock, true, true, v>), grid, block, 0, stream, a);
+            hipLaunchKernelGGL((k_backward<n, true, true, v>), grid, dim3(n), 0, stream, a);
         else if (gin)
-            hipLaunchKernelGGL((k_backward<kBwdBlock, true, false, v>), grid, block, 0, stream, a);
+            hipLaunchKernelGGL((k_backward<n, true, false, v>), grid, dim3(n), 0, stream, a);
         else
-            hipLaunchKernelGGL((k_backward<kBwdBlock, false, true, v>), grid, block, 0, stream, a);
+            hipLaunchKernelGGL((k_backward<n, false, true, v>), grid, dim3(n), 0, stream, a);
     };
-    if (vec)
-        go(std::true_type{});
+    if (vec && blocks < kBwdWidePerCU * device_cus())
+        go(IC<kBwdWide>{}, std::true_type{});
+    else if (vec)
+        go(IC<kBwdBlock>{}, std::true_type{});
     else
-        go(std::false_type{});
+        go(IC<kBwdBlock>{}, std::false_type{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return DSK_EHIP;
     if (goff) {

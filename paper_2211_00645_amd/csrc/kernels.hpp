@@ -1454,6 +1454,16 @@ __device__ __forceinline__ double block_sum(double v, double *lds) {
 // (equal to summing gD[x'] * (S[x'-k-1] - S[x'-k]) over x').
 // Workgroups are plane-major: block = n * G + g covers rows
 // [g * rows_per_block, ...) of plane n.
+//
+// VEC: the block's rows are one list of groups of 4 adjacent columns, thread
+// t takes groups t, t + BLOCK, ..., so narrow rows fill the workgroup
+// (182x1152x64 into 337: 103 us with a row at a time, 16 threads of 256 at
+// work; now 31).  A row's last group is moved back to end at its end and adds
+// only the columns the group before does not.  A group's 5 gradient values
+// come from one 16-byte and one 4-byte load (per pixel where the window leaves
+// [0, W)), the stack's 4 from one 16-byte load, and the adjoint leaves in one
+// 16-byte store, all at any 4-byte boundary.  Memory bound: 12 bytes a raw
+// pixel; 256x512x1024 0.300 ms, 5.4 TB/s.
 template <int BLOCK, bool GIN, bool GOFF, bool VEC>
 __global__ __launch_bounds__(BLOCK) void k_backward(BwdArgs a) {
     __shared__ double lds[BLOCK / 64];
@@ -1463,56 +1473,70 @@ __global__ __launch_bounds__(BLOCK) void k_backward(BwdArgs a) {
     const int r0 = g * a.rows_per_block;
     const int r1 = min(a.R, r0 + a.rows_per_block);
     const int64_t C = a.C, W = a.W;
+    const int64_t nr = (int64_t)a.N * a.R;
     double part = 0.0;
-    for (int r = r0; r < r1; ++r) {
-        const int64_t rowi = (int64_t)n * a.R + r, nr = (int64_t)a.N * a.R;
-        const float *grow = bounded(a.gvol + rowi * W, W, a.gvol, a.gvol + nr * W);
-        const float *srow = a.in;
-        if constexpr (GOFF) srow = bounded(a.in + rowi * C, C, a.in, a.in + nr * C);
-        float *orow = nullptr;
-        if constexpr (GIN) orow = bounded(a.gin + rowi * C, C, a.gin, a.gin + nr * C);
-        if constexpr (VEC) {
-            // 4 adjacent raw columns per thread: their 5 gradient values
-            // from one 16-byte and one 4-byte load (per pixel where the
-            // window leaves [0, W)), the stack and the adjoint in 16 bytes
-            for (int64_t c = 4 * (int64_t)threadIdx.x; c < C; c += 4 * BLOCK) {
-                const int64_t x = c + pc.k;
-                float gv[5];
-                if (x >= 0 && x + 5 <= W) {
-                    float4 q;
-                    __builtin_memcpy(&q, grow + x, sizeof(q));   // 4-byte aligned
-                    gv[0] = q.x;
-                    gv[1] = q.y;
-                    gv[2] = q.z;
-                    gv[3] = q.w;
-                    gv[4] = grow[x + 4];
-                } else {
+    if constexpr (VEC) {
+        const int per_row = (a.C + 3) / 4;
+        const int row_step = BLOCK / per_row, grp_step = BLOCK - row_step * per_row;
+        int r = r0 + (int)threadIdx.x / per_row, q = (int)threadIdx.x % per_row;
+        while (r < r1) {
+            const int64_t rowi = (int64_t)n * a.R + r;
+            const float *grow = bounded(a.gvol + rowi * W, W, a.gvol, a.gvol + nr * W);
+            const int64_t c = min(4 * q, a.C - 4);
+            const int dup = 4 * q - (int)c;      // columns of the group before
+            const int64_t x = c + pc.k;
+            float gv[5];
+            f32x4 sv = {0.0f, 0.0f, 0.0f, 0.0f};
+            if constexpr (GOFF)
+                sv = *(const f32x4_any *)bounded(a.in + rowi * C + c, 4, a.in, a.in + nr * C);
+            if (x >= 0 && x + 5 <= W) {
+                const f32x4 v = *(const f32x4_any *)(grow + x);
+                gv[0] = v.x;
+                gv[1] = v.y;
+                gv[2] = v.z;
+                gv[3] = v.w;
+                gv[4] = grow[x + 4];
+            } else {
 #pragma unroll
-                    for (int i = 0; i < 5; ++i) gv[i] = load_px(grow, x + i, W);
-                }
-                if constexpr (GIN) {
-                    f32x4 o;
-                    o.x = fmaf(pc.whi, gv[0], pc.wlo * gv[1]);
-                    o.y = fmaf(pc.whi, gv[1], pc.wlo * gv[2]);
-                    o.z = fmaf(pc.whi, gv[2], pc.wlo * gv[3]);
-                    o.w = fmaf(pc.whi, gv[3], pc.wlo * gv[4]);
-                    store_f32x4<true>(orow + c, o);
-                }
-                if constexpr (GOFF) {
-                    const float4 sv = *(const float4 *)(srow + c);   // 16-byte aligned
-                    part += (double)sv.x * ((double)gv[1] - (double)gv[0]);
-                    part += (double)sv.y * ((double)gv[2] - (double)gv[1]);
-                    part += (double)sv.z * ((double)gv[3] - (double)gv[2]);
-                    part += (double)sv.w * ((double)gv[4] - (double)gv[3]);
+                for (int i = 0; i < 5; ++i) gv[i] = load_px(grow, x + i, W);
+            }
+            if constexpr (GIN) {
+                f32x4 o;
+                o.x = fmaf(pc.whi, gv[0], pc.wlo * gv[1]);
+                o.y = fmaf(pc.whi, gv[1], pc.wlo * gv[2]);
+                o.z = fmaf(pc.whi, gv[2], pc.wlo * gv[3]);
+                o.w = fmaf(pc.whi, gv[3], pc.wlo * gv[4]);
+                store_f32x4<true, f32x4_any>(
+                    bounded(a.gin + rowi * C + c, 4, a.gin, a.gin + nr * C), o);
+            }
+            if constexpr (GOFF) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const double t = (double)sv[i] * ((double)gv[i + 1] - (double)gv[i]);
+                    part += i >= dup ? t : 0.0;
                 }
             }
-        } else {
+            r += row_step;
+            q += grp_step;
+            if (q >= per_row) {
+                q -= per_row;
+                ++r;
+            }
+        }
+    } else {
+        for (int r = r0; r < r1; ++r) {
+            const int64_t rowi = (int64_t)n * a.R + r;
+            const float *grow = bounded(a.gvol + rowi * W, W, a.gvol, a.gvol + nr * W);
             for (int64_t c = threadIdx.x; c < C; c += BLOCK) {
                 const int64_t x = c + pc.k;
                 const float g0 = load_px(grow, x, W);
                 const float g1 = load_px(grow, x + 1, W);
-                if constexpr (GIN) orow[c] = fmaf(pc.whi, g0, pc.wlo * g1);
-                if constexpr (GOFF) part += (double)srow[c] * ((double)g1 - (double)g0);
+                if constexpr (GIN)
+                    *bounded(a.gin + rowi * C + c, 1, a.gin, a.gin + nr * C) =
+                        fmaf(pc.whi, g0, pc.wlo * g1);
+                if constexpr (GOFF)
+                    part += (double)*bounded(a.in + rowi * C + c, 1, a.in, a.in + nr * C) *
+                            ((double)g1 - (double)g0);
             }
         }
     }
