@@ -127,9 +127,15 @@ static hipError_t fwd_launch_vec(FwdArgs<TIn> a, int64_t tiles, int64_t edge, in
                               : vec_resident_per_cu<TIn, B, PT / 4, U, false, false, GEN>()) *
               device_cus();
     // without a volume a frame whose tiles do not all fit at once is
-    // not paced: its later tiles would wait out a schedule that began
-    // before they started
-    if (!a.vol && pace_gbs > 0 && tiles * a.R > cap) pace_gbs = 0;
+    // paced only if its tiles can be dispatched in the order in which they
+    // meet the planes (a uniform scan): other frames' later tiles would wait
+    // out a schedule that began before they started
+    if (!a.vol && pace_gbs > 0 && tiles * a.R > cap) {
+        if (a.offs || a.shift == 0.0)
+            pace_gbs = 0;
+        else
+            a.sweep = a.shift > 0.0 ? 1 : -1;
+    }
     auto launch_rows = [&](FwdArgs<TIn> f, int64_t f_edge) {
         if (pace_gbs > 0) {
             // one tile's share of a plane's bytes, timed at pace_gbs
@@ -258,6 +264,10 @@ constexpr int64_t kFewTilesPerCU = 6;
 //    us: 300x400x1024 uint16 (246 MB) 69.5 against 74.0, 128x512x2000 (262 MB)
 //    63.0 against 66.3; 256x512x1600 (419 MB) 111 against 106 paced
 constexpr int64_t kSmallProjBytes = 300000000;
+//  * tiles that meet few planes spend them in the planes before and after the
+//    whole steps of the pipeline, one at a time: 2 planes a step, 50x1304x87
+//    into 3653 columns (5 planes a tile) 26.7 -> 22.7 us
+constexpr int64_t kFewPlanes = 16;
 
 static dsk_tune default_tune(const void *in, int in_is_f32, dsk_dims d, int64_t in_plane,
                       const float *vol, int64_t width) {
@@ -265,6 +275,9 @@ static dsk_tune default_tune(const void *in, int in_is_f32, dsk_dims d, int64_t 
     if (!vol) {
         dsk_tune t = kDefaultProjTune;
         if (stack_bytes <= kSmallProjBytes) t.pace_gbs = 0;
+        // about how many planes a tile meets in a uniform scan: (C + 256) N /
+        // (W - C)
+        if (((int64_t)d.cols + 256) * d.planes <= kFewPlanes * (width - d.cols)) t.unroll = 2;
         return t;
     }
     dsk_tune t = kDefaultTune;
@@ -325,7 +338,7 @@ int launch_forward_default(const void *in, int in_is_f32, dsk_dims d, const InLa
             using TIn = std::remove_const_t<std::remove_pointer_t<decltype(p)>>;
             const FwdArgs<TIn> a{p, vol, psum, pmax, offs, shift, (double)origin, width,
                                  d.planes, d.rows, d.cols, lay.row, lay.plane, lay.lo, lay.hi,
-                                 0u, 0u, 0, 0, (int64_t)d.rows * width, 0};
+                                 0u, 0u, 0, 0, (int64_t)d.rows * width, 0, 0};
             return hip_status(launch_split(a, tiles, stream));
         };
         return in_is_f32 ? go((const float *)in) : go((const uint16_t *)in);
@@ -351,12 +364,12 @@ int launch_forward_layout(const void *in, int in_is_f32, dsk_dims d, const InLay
     if (in_is_f32) {
         FwdArgs<float> a{(const float *)in, vol, psum, pmax, offs, shift, (double)origin,
                          width, d.planes, d.rows, d.cols, lay.row, lay.plane, lay.lo, lay.hi,
-                         0u, 0u, 0, (int32_t)edge, (int64_t)d.rows * width, align ? 1 : 0};
+                         0u, 0u, 0, (int32_t)edge, (int64_t)d.rows * width, align ? 1 : 0, 0};
         e = fwd_dispatch<float>(a, t, vec, tiles, edge, stream);
     } else {
         FwdArgs<uint16_t> a{(const uint16_t *)in, vol, psum, pmax, offs, shift, (double)origin,
                             width, d.planes, d.rows, d.cols, lay.row, lay.plane, lay.lo, lay.hi,
-                            0u, 0u, 0, (int32_t)edge, (int64_t)d.rows * width, align ? 1 : 0};
+                            0u, 0u, 0, (int32_t)edge, (int64_t)d.rows * width, align ? 1 : 0, 0};
         e = fwd_dispatch<uint16_t>(a, t, vec, tiles, edge, stream);
     }
     return hip_status(e);

@@ -190,6 +190,10 @@ struct FwdArgs {
     // floats: every row's tiles start on a 128-byte boundary of the volume
     // (the host adds a tile's worth of room: 7 groups per row).
     int32_t align_tiles;
+    // Launches without a volume: 0, or the order in which the column tiles
+    // meet the planes (1: left to right, -1: right to left), in which they are
+    // then dispatched.
+    int32_t sweep;
 };
 
 // Plane pacing: a wavefront that reaches plane n before t0 + n * tau sleeps
@@ -1005,6 +1009,9 @@ struct VecTile {
             }
         }
         if (n_lo >= n_hi) return;
+        // a tile that starts after the first round's begins its planes at once
+        if (a.pace_cap > 0 && (int64_t)blockIdx.x >= a.pace_cap)
+            t0 -= ((uint64_t)n_lo * taug) >> 8;
         // the pipelined range: whole steps of U planes, aligned (so a step
         // never spans two chunks), rows at a stack end excluded
         const int lo = n_lo + ((first_special == 0 && n_lo == 0) ? 1 : 0);
@@ -1062,12 +1069,13 @@ struct VecTile {
             run_projections();
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int64_t o = (int64_t)r * W + xcol(g) + i, rw = (int64_t)a.R * W;
-                if (a.psum) *bounded(a.psum + o, 1, a.psum, a.psum + rw) = (float)acc[g][i];
-                if (a.pmax) *bounded(a.pmax + o, 1, a.pmax, a.pmax + rw) = mx[g][i];
-            }
+            const int64_t o = (int64_t)r * W + xcol(g), rw = (int64_t)a.R * W;
+            if (a.psum)
+                *(f32x4_any *)bounded(a.psum + o, 4, a.psum, a.psum + rw) = f32x4{
+                    (float)acc[g][0], (float)acc[g][1], (float)acc[g][2], (float)acc[g][3]};
+            if (a.pmax)
+                *(f32x4_any *)bounded(a.pmax + o, 4, a.pmax, a.pmax + rw) =
+                    f32x4{mx[g][0], mx[g][1], mx[g][2], mx[g][3]};
         }
     }
 };
@@ -1165,10 +1173,16 @@ __device__ __forceinline__ int middle_out(int k, int T) {
 
 // Block b of a plain launch.  With a volume: row-major tiles (paced launches
 // start workgroups in id order, a batch of resident ones at a time).
-// Without: the tiles of one column rank for every row, ranks middle-out, so
-// the heaviest tiles start first (in a uniform scan a column tile meets the
-// most planes at the frame's centre, the fewest at its ends) and lighter
-// ones fill in behind them.
+// Without: the tiles of one column rank for every row.  Where all tiles are
+// resident at once, or where the planes a tile meets are not known, ranks go
+// middle-out, so the heaviest tiles start first (in a uniform scan a column
+// tile meets the most planes at the frame's centre, the fewest at its ends)
+// and lighter ones fill in behind them.  A uniform scan with more tiles than
+// are resident goes in the order in which its tiles meet the planes (sweep):
+// the first tiles meet few planes, all early, and make room for the last
+// ones, which meet few, all late, so that neighbouring tiles keep reading the
+// same planes at about the same time, paced, and share the lines that two of
+// their windows cover.
 template <typename TIn, int BLOCK, int G, int UNR, bool NT, bool VOL, bool GEN>
 __device__ __forceinline__ void fwd_vec_block(const FwdArgs<TIn> &a, int tiles_x, int64_t b) {
     // the edge columns' workgroups come first: they are short and start
@@ -1189,7 +1203,7 @@ __device__ __forceinline__ void fwd_vec_block(const FwdArgs<TIn> &a, int tiles_x
         } else {
             const int k = (int)(b / a.R);
             r = (int)(b - (int64_t)k * a.R);
-            xt = middle_out(k, tiles_x);
+            xt = a.sweep == 0 ? middle_out(k, tiles_x) : (a.sweep > 0 ? k : tiles_x - 1 - k);
         }
         VecTile<TIn, BLOCK, G, UNR, NT, VOL, GEN> vt(a, r, xt, (int)threadIdx.x);
         vt.run();
@@ -1400,6 +1414,7 @@ __global__ __launch_bounds__(BLOCK, vec_waves_per_eu(PT >= 8 ? 2 : 1, UNR, VOL, 
         a.edge_wg = jb.edge_blocks;
         a.vol_plane = (int64_t)jb.R * jb.W;
         a.align_tiles = 0;
+        a.sweep = 0;
         const int64_t lt = t - jb.tile_begin;
         if constexpr (PT >= 4) {
             if (jb.vec == VEC_ALIGNED) {
