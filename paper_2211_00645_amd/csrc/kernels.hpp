@@ -1182,7 +1182,8 @@ __device__ __forceinline__ int middle_out(int k, int T) {
 // the first tiles meet few planes, all early, and make room for the last
 // ones, which meet few, all late, so that neighbouring tiles keep reading the
 // same planes at about the same time, paced, and share the lines that two of
-// their windows cover.
+// their windows cover (512x512x2048 seen from the top, 34 tiles a compute unit
+// where 28 are resident: 268 us unpaced and middle-out, 228 so).
 template <typename TIn, int BLOCK, int G, int UNR, bool NT, bool VOL, bool GEN>
 __device__ __forceinline__ void fwd_vec_block(const FwdArgs<TIn> &a, int tiles_x, int64_t b) {
     // the edge columns' workgroups come first: they are short and start

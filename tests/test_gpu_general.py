@@ -61,3 +61,19 @@ def test_volume_off_alignment():
         dsk.deskew(st, 30.0, 0.4, 0.115, out={"vol": vol})
         torch.cuda.synchronize()
         assert torch.equal(vol, ref["vol"]), off
+
+
+@pytest.mark.parametrize("step", [16.0, -16.0])
+@pytest.mark.parametrize("cols", [300, 301])
+def test_sweep_order(step, cols):
+    """Paced projections of a uniform scan with more tiles than are resident
+    (dispatched in plane order, later tiles starting their planes at once)."""
+    st = _stack((9, 1800, cols), "u16", 0, 4)
+    geo = (35.0, step, 0.115)
+    ref = dsk.deskew(st, *geo, vol=False, tune=SCALAR)
+    assert 1800 * (-(-ref["width"] // 256)) > 32 * 256
+    for tune in (None, dict(unroll=4, pace_gbs=9000), dict(unroll=2, pace_gbs=500)):
+        out = dsk.deskew(st, *geo, vol=False, tune=tune)
+        torch.cuda.synchronize()
+        for k in ("psum", "pmax"):
+            assert torch.equal(out[k], ref[k]), (tune, k)
