@@ -248,7 +248,7 @@ int dsk_backward_f32_noalloc(const float *in, const float *grad_vol,
  * one graph launch.  The graph holds either one persistent kernel (one
  * workgroup per compute-unit slot walks a shared list of (stack, row,
  * column-tile) items: no per-launch tails, best for many small stacks) or
- * one plain paced launch per job (each job's wavefronts keep to one
+ * one plain launch per job (each job's wavefronts keep to one
  * schedule: best for large stacks), in the default shape or in each job
  * frame's tuned shape, whichever the autotuner measures faster.  Each job's outputs are bitwise identical to its own
  * dsk_deskew_offsets_u16 / dsk_deskew_u16 call in either mode.
@@ -305,9 +305,11 @@ size_t dsk_jobs_table_bytes(int n_jobs);
 
 /* One persistent launch over jobs given per call (the serving path).
  * table_host: host buffer of dsk_jobs_table_bytes(n_jobs) bytes, ideally
- * pinned; it is encoded here and copied to table_dev with hipMemcpyAsync on
+ * pinned; it is encoded here and, for lists of more than 32 jobs or a shape
+ * other than the default's, copied to table_dev with hipMemcpyAsync on
  * `stream`, so it must stay unchanged until that copy completes (record an
- * event).  table_dev: device buffer of the same size.  tune NULL: the
+ * event); shorter lists travel in the launch's arguments.  table_dev: device
+ * buffer of the same size.  tune NULL: the
  * library default, paced only when every job has one frame (dims and
  * out_width), since pacing helps wavefronts that move in lockstep and
  * holds back a grid whose tiles belong to stacks of different sizes. */

@@ -4,6 +4,7 @@
 // buffers (on-disk cache of the choice), captured in a HIP graph.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -20,11 +21,11 @@
 using namespace dsk;
 
 // One persistent launch: `count` job records from `first` in the table, all
-// writing a volume or none (each kind has its own kernel), their tiles
+// writing a volume or none (each kind has its own kernel), their shares
 // numbered from 0.
 struct SubLaunch {
     int first = 0, count = 0;
-    int64_t total = 0;
+    int64_t total = 0;      // shares of all jobs
     int grid = 0;
     bool vol = false;
 };
@@ -47,14 +48,25 @@ struct dsk_batch {
 namespace {
 
 using JobsKernel = void (*)(const JobDev *, int, int64_t);
+using JobsArgKernel = void (*)(JobArgs, int, int64_t);
 
 JobsKernel pick_kernel(const dsk_tune &t, bool vol) {
     return dispatch_tune(t, [vol](auto B, auto P, auto U, auto NT) -> JobsKernel {
         constexpr int b = decltype(B)::value, p = decltype(P)::value, u = decltype(U)::value;
         // launches without a volume only read: no store kind to choose
-        if (vol) return k_forward_jobs<b, p, u, decltype(NT)::value, true>;
-        return k_forward_jobs<b, p, u, false, false>;
+        if (vol) return k_forward_jobs<b, p, u, decltype(NT)::value, true, const JobDev *>;
+        return k_forward_jobs<b, p, u, false, false, const JobDev *>;
     });
+}
+
+// The same kernel with the table in its arguments, built for the default
+// shapes only; null for any other.
+JobsArgKernel pick_arg_kernel(const dsk_tune &t, bool vol) {
+    if (t.block != 64 || t.per_thread != 4) return nullptr;
+    if (vol && t.unroll == 2 && t.nt_store == 1)
+        return k_forward_jobs<64, 4, 2, true, true, JobArgs>;
+    if (!vol && t.unroll == 4) return k_forward_jobs<64, 4, 4, false, false, JobArgs>;
+    return nullptr;
 }
 
 int validate_job(const dsk_job &j) {
@@ -64,15 +76,21 @@ int validate_job(const dsk_job &j) {
 }
 
 // Job table for a launch shape: the jobs that write a volume first, then the
-// others, each part numbering its tiles from 0.  Fills one SubLaunch per
+// others, the jobs of most planes ahead in each part (their tiles take longest,
+// so they start first), each part numbering its shares from 0.  Fills one SubLaunch per
 // non-empty part (grid still 0) and returns their number, or < 0.
 int encode_table(const dsk_job *jobs, int n, const dsk_tune &t, JobDev *out, SubLaunch subs[2]) {
+    std::vector<int> order((size_t)n);
+    for (int i = 0; i < n; ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
+        return jobs[x].dims.planes > jobs[y].dims.planes;
+    });
     int ns = 0, k = 0;
     for (int pass = 0; pass < 2; ++pass) {
         const bool vol = pass == 0;
         const int first = k;
         int64_t begin = 0;
-        for (int i = 0; i < n; ++i) {
+        for (int i : order) {
             const dsk_job &j = jobs[i];
             if ((j.vol != nullptr) != vol) continue;
             const int vec = vec_mode(t, j.dims, j.out_width, j.in, 0, j.vol,
@@ -89,7 +107,7 @@ int encode_table(const dsk_job *jobs, int n, const dsk_tune &t, JobDev *out, Sub
             r.shift = j.shift_px;
             r.origin = (double)j.origin;
             r.W = j.out_width;
-            r.tile_begin = begin;
+            r.begin = begin;
             r.N = j.dims.planes;
             r.R = j.dims.rows;
             r.C = j.dims.cols;
@@ -98,7 +116,7 @@ int encode_table(const dsk_job *jobs, int n, const dsk_tune &t, JobDev *out, Sub
             r.edge_blocks = (int32_t)eb;
             r.tau256 = 0;
             out[k++] = r;
-            begin += tx * j.dims.rows + eb;
+            begin += r.share();
             if (begin < 0 || begin > (int64_t(1) << 50)) return -1;
         }
         if (k > first) {
@@ -114,8 +132,8 @@ int encode_table(const dsk_job *jobs, int n, const dsk_tune &t, JobDev *out, Sub
     return ns;
 }
 
-// Resident workgroups for the persistent grid.
-int persistent_grid(const dsk_tune &t, bool vol, int64_t total_tiles) {
+// Resident workgroups for the persistent grid, a multiple of the 8 XCDs.
+int persistent_grid(const dsk_tune &t, bool vol, int64_t shares) {
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return -1;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
@@ -125,10 +143,10 @@ int persistent_grid(const dsk_tune &t, bool vol, int64_t total_tiles) {
         return -1;
     if (per_cu < 1) per_cu = 1;
     if (t.wg_per_cu > 0 && t.wg_per_cu < per_cu) per_cu = t.wg_per_cu;
-    int64_t g = (int64_t)cus * per_cu;
-    if (g > total_tiles) g = total_tiles;
+    int64_t g = (int64_t)cus * per_cu / 8;
+    if (g > shares) g = shares;
     if (g < 1) g = 1;
-    return (int)g;
+    return (int)(8 * g);
 }
 
 // Plane pacing of each job: every resident workgroup of the persistent grid
@@ -171,6 +189,25 @@ hipError_t launch_jobs(const JobDev *table, const SubLaunch *subs, int ns, const
                             dim3(t.block), args, 0, s);
     }
     return e;
+}
+
+// The launches of a table of at most kArgJobs records with the records in
+// their arguments; false, with nothing launched, where the shape has no such
+// kernel.
+bool launch_jobs_by_value(const JobDev *table, const SubLaunch *subs, int ns, const dsk_tune &t,
+                          hipStream_t s, hipError_t *e) {
+    for (int i = 0; i < ns; ++i)
+        if (!pick_arg_kernel(t, subs[i].vol)) return false;
+    *e = hipSuccess;
+    for (int i = 0; i < ns && *e == hipSuccess; ++i) {
+        JobArgs a;
+        std::memset(&a, 0, sizeof a);
+        std::memcpy(a.j, table + subs[i].first, sizeof(JobDev) * (size_t)subs[i].count);
+        hipLaunchKernelGGL(pick_arg_kernel(t, subs[i].vol), dim3(subs[i].grid), dim3(64), 0, s, a,
+                           subs[i].count, subs[i].total);
+        *e = hipGetLastError();
+    }
+    return true;
 }
 
 int log2_bucket(double v) { return v <= 1.0 ? 0 : (int)std::floor(std::log2(v)); }
@@ -454,12 +491,15 @@ extern "C" int dsk_jobs_launch(const dsk_job *jobs, int n_jobs, void *table_host
     }
     JobDev *host = (JobDev *)table_host;
     SubLaunch subs[2];
+    hipError_t e = hipSuccess;
     const int ns = encode_table(jobs, n_jobs, t, host, subs);
     if (ns <= 0) return DSK_ESHAPE;
     const int st = plan_launches(t, host, subs, ns);
     if (st != DSK_OK) return st;
-    hipError_t e = hipMemcpyAsync(table_dev, host, dsk_jobs_table_bytes(n_jobs),
-                                  hipMemcpyHostToDevice, stream);
+    // a short table travels in the launch's arguments: no copy before it
+    if (n_jobs <= kArgJobs && launch_jobs_by_value(host, subs, ns, t, stream, &e)) return hip_status(e);
+    e = hipMemcpyAsync(table_dev, host, dsk_jobs_table_bytes(n_jobs), hipMemcpyHostToDevice,
+                       stream);
     if (e == hipSuccess) e = launch_jobs((const JobDev *)table_dev, subs, ns, t, stream);
     return hip_status(e);
 }

@@ -244,20 +244,23 @@ static bool tiles_aligned(const float *vol, dsk_dims d, int64_t width, const dsk
 //    leave partial lines at both ends of every store run and their cliff
 //    lies between 5200 and 5400: 201x487x1531 uint16 4022 paced 5700, 5050
 //    at 5200; float32 256x512x1024 into 1793 columns 4160 at 5700, 5110 at
-//    5100.  5100 keeps 100 of margin;
-//  * up to kSmallBytes moved and kSmallPlanes planes the last-level cache
-//    absorbs most of the writes and the wavefronts cannot drift far apart,
-//    so a launch does better unpaced: 64x512x2048 uint16 (435 MB) 6496
-//    against 5409, 48x512x2048 float32 (425 MB) 6437 against 5476.  Unaligned
-//    16-bit frames of that size do better paced at 5700 (80x511x1023: 5286
-//    against 4971), and more planes need the pacing (256x256x512, 392 MB:
-//    4441 against 3809);
+//    5100.  5100 keeps 100 of margin.  Up to kPartialLineBytes moved the
+//    last-level cache joins the partial lines and 5700 holds: 128x511x1023
+//    (502 MB) 5450 against 4884 at 5100, 200x300x600 (352 MB) 67.5 us against
+//    74.3;
+//  * up to kSmallBytes moved and kSmallPlanes planes that cache absorbs most
+//    of the writes and the wavefronts cannot drift far apart, so a launch
+//    does better unpaced, in us over stacks in turn: 64x512x1024 uint16 (231
+//    MB) 42.4 against 45.4, 40x1000x800 (210 MB) 36.4 against 42.0;
+//    64x512x2048 (426 MB) 90.0 against 80.4 paced.  Unaligned 16-bit frames do
+//    better paced at any size (80x511x1023: 5286 GB/s against 4971), and more
+//    planes need the pacing (256x256x512: 4441 against 3809);
 //  * with few wavefronts a compute unit a 4-plane pipeline keeps enough
 //    loads in flight: 256x256x512 (5 wavefronts) 4409 -> 5140, 128x320x512
 //    (5) 45.4 -> 39.8 us; from 7 on the two are equal, from 14 on 2 planes
 //    do better.
 constexpr int kPartialLinePace = 5100;
-constexpr int64_t kSmallBytes = 450000000;
+constexpr int64_t kSmallBytes = 250000000, kPartialLineBytes = 500000000;
 constexpr int32_t kSmallPlanes = 100;
 constexpr int64_t kFewTilesPerCU = 6;
 //  * without a volume, stacks of up to kSmallProjBytes do better unpaced, in
@@ -285,11 +288,10 @@ static dsk_tune default_tune(const void *in, int in_is_f32, dsk_dims d, int64_t 
     if (vec == VEC_NONE) return t;
     const int64_t bytes = stack_bytes + 4 * (int64_t)d.planes * d.rows * width;
     const bool aligned = tiles_aligned(vol, d, width, t, vec);
-    if (bytes <= kSmallBytes && d.planes <= kSmallPlanes) {
-        if (aligned || in_is_f32) t.pace_gbs = 0;
-    } else if (!aligned) {
+    if (bytes <= kSmallBytes && d.planes <= kSmallPlanes && (aligned || in_is_f32))
+        t.pace_gbs = 0;
+    else if (!aligned && bytes > kPartialLineBytes)
         t.pace_gbs = kPartialLinePace;
-    }
     if (tiles_x(width, t, vec) * d.rows <= kFewTilesPerCU * device_cus()) t.unroll = 4;
     return t;
 }
