@@ -15,18 +15,27 @@ import torch
 from . import _lib as L
 
 
+# The current stream's handle without a Stream object around it (about 3 us of
+# a call that takes 12); torch builds without it go through the object.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None and _device is not None and torch.cuda.is_initialized():
+        return _raw_stream(_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _vp(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _dims(shape):
-    n, r, c = (int(v) for v in shape)
-    return L.Dims(n, r, c)
+    n, r, c = shape
+    return L.Dims(int(n), int(r), int(c))
 
 
 def _check_stack(x, dtypes=(torch.uint16, torch.float32)):
