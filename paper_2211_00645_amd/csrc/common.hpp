@@ -167,6 +167,9 @@ int launch_forward_default(const void *in, int in_is_f32, dsk_dims d, const InLa
 // arguments.
 hipError_t launch_split(const FwdArgs<uint16_t> &a, int64_t tiles, hipStream_t s);
 hipError_t launch_split(const FwdArgs<float> &a, int64_t tiles, hipStream_t s);
+// The row kernel's launch for projections (split.hip), on checked arguments.
+hipError_t launch_project_rows(const FwdArgs<uint16_t> &a, hipStream_t s);
+hipError_t launch_project_rows(const FwdArgs<float> &a, hipStream_t s);
 
 // Launchers (deskew.hip) used by the other translation units.
 int launch_forward(const void *in, int in_is_f32, dsk_dims d, const double *offs,

@@ -446,8 +446,14 @@ __device__ __forceinline__ int edge_col(const RowGeo &g, int W, int j) {
 //
 // ACC: the tile keeps the sums and maxima (the split kernel takes them from
 // LDS instead).
-template <typename TIn, int BLOCK, int G, int UNR, bool NT, bool VOL, bool GEN, bool ACC = true>
+//
+// ROWS > 1 (general, without a volume, one wavefront and group per lane): the
+// wavefront's lanes cover ROWS rows of 64 / ROWS groups each, rows ROWS * row
+// on; lanes of rows past the last repeat it.
+template <typename TIn, int BLOCK, int G, int UNR, bool NT, bool VOL, bool GEN, bool ACC = true,
+          int ROWS = 1>
 struct VecTile {
+    static_assert(ROWS == 1 || (GEN && !VOL && BLOCK == 64 && G == 1), "rows of one wavefront");
     enum { OUT = 0, IN = 1, MIXED = 2 };
     using Win = RawWin<TIn>;
     const FwdArgs<TIn> &a;
@@ -462,6 +468,8 @@ struct VecTile {
     float *op0;                        // volume row r of plane 0 (or null)
     // columns from ca: the lane's group, the wavefront's first and last
     int gx[G], pfirst[G], plast[G];
+    // the lane's row after r, and its first element after row r's (ROWS > 1)
+    int lrow, lelem;
     bool alive;
     uint64_t t0;                       // pacing origin (this wavefront's start)
     uint32_t tau;                      // pacing period per plane, 1/256 ticks (0 = none)
@@ -476,7 +484,7 @@ struct VecTile {
 
     // tid: this thread's place in the tile's BLOCK threads
     __device__ __forceinline__ VecTile(const FwdArgs<TIn> &args, int row, int tile, int tid)
-        : a(args), r(row), W((int)args.W), C(args.C), N(args.N) {
+        : a(args), r(row * ROWS), W((int)args.W), C(args.C), N(args.N) {
         const RowGeo rg = GEN ? RowGeo{0, (W + 3) / 4} : row_geo(r, W);
         ca = rg.ca;
         ng = rg.ng;
@@ -484,7 +492,9 @@ struct VecTile {
         ostep = a.vol_plane;
         wv = __builtin_amdgcn_readfirstlane(tid >> 6);
         lane = tid & 63;
-        int base = tile * BLOCK * G;
+        int base = tile * (BLOCK * G / ROWS);
+        lrow = ROWS > 1 ? min(lane / (64 / ROWS), args.R - 1 - r) : 0;
+        lelem = lrow * (int)args.in_row;
         if constexpr (VOL && !GEN) {
             // shift the row's tile grid back by the groups that lie between
             // the previous 128-byte boundary of the volume and the row's
@@ -509,7 +519,8 @@ struct VecTile {
         // the readable start and only plane N-1 can end closer than 8 to its end
         const int64_t g0 = (int64_t)r * a.in_row;
         first_special = (g0 - 8 < -a.in_lo) ? 0 : -1;
-        last_special = ((int64_t)(N - 1) * rstep + g0 + C + 8 > a.in_hi) ? N - 1 : -1;
+        const int64_t g1 = ROWS > 1 ? (int64_t)min(r + ROWS - 1, a.R - 1) * a.in_row : g0;
+        last_special = ((int64_t)(N - 1) * rstep + g1 + C + 8 > a.in_hi) ? N - 1 : -1;
         rp0 = a.in + (int64_t)r * a.in_row;
         op0 = VOL ? a.vol + (int64_t)r * W : nullptr;
         tau = a.tau256;
@@ -536,9 +547,9 @@ struct VecTile {
                 plast[g] = 4 * max(0, min(w0 + 63, ng - 1));
             } else {
                 const int w0 = base + 64 * G * wv + g;
-                gx[g] = 4 * min(w0 + G * lane, ng - 1);
+                gx[g] = 4 * min(w0 + G * (lane % (64 / ROWS)), ng - 1);
                 pfirst[g] = 4 * min(w0, ng - 1);
-                plast[g] = 4 * min(w0 + G * 63, ng - 1);
+                plast[g] = 4 * min(w0 + G * (64 / ROWS - 1), ng - 1);
             }
             if constexpr (GEN) {
                 gx[g] = min(gx[g], W - 4);
@@ -553,12 +564,15 @@ struct VecTile {
         }
     }
 
+    // Parity of the row start of the lane's row (GEN: in a plane of packed v).
+    __device__ __forceinline__ int row_par(int v) const { return ROWS > 1 ? v + lelem : v; }
+
     // lo_off and hi_off of a plane (GEN: with its row start's parity)
     __device__ __forceinline__ int lo_of(int v) const {
-        return GEN && Win::kAlign == 2 ? -8 + (v & 1) : lo_off;
+        return GEN && Win::kAlign == 2 ? -8 + (row_par(v) & 1) : lo_off;
     }
     __device__ __forceinline__ int hi_of(int v) const {
-        return GEN && Win::kAlign == 2 ? C - 1 - ((C - 1 + v) & 1) : hi_off;
+        return GEN && Win::kAlign == 2 ? C - 1 - ((C - 1 + row_par(v)) & 1) : hi_off;
     }
 
     __device__ __forceinline__ int xcol(int g) const { return ca + gx[g]; }
@@ -629,7 +643,7 @@ struct VecTile {
     // First needed pixel's place in the window of group g (v the plane's
     // packed start/shift), and that pixel's position in the row.
     __device__ __forceinline__ int win_shift(int g, int v) const {
-        return GEN ? (((v >> 1) + v + gx[g]) & (Win::kAlign - 1)) : (v & 1);
+        return GEN ? (((v >> 1) + row_par(v) + gx[g]) & (Win::kAlign - 1)) : (v & 1);
     }
     __device__ __forceinline__ int first_px(int g, int v) const {
         return (v >> 1) + (GEN ? 0 : (v & 1)) + gx[g];
@@ -646,6 +660,7 @@ struct VecTile {
             const int lo = lo_of(v), hi = hi_of(v);
             off = off < lo ? lo : (off > hi ? hi : off);
         }
+        if constexpr (ROWS > 1) off += lelem;
         w.load(bounded(rp + off, Win::kLen, a.in - a.in_lo, a.in + a.in_hi));
     }
 
@@ -676,13 +691,14 @@ struct VecTile {
                                            float d[4]) {
         constexpr int K = Win::kAlign;
         const TIn *rp = rp0 + (int64_t)n * rstep;
+        if constexpr (ROWS > 1) rp += lelem;
         const int v = __builtin_amdgcn_readlane(win, li);
         const int sh = win_shift(g, v);
         const float wlo = lane_f(wlo_l, li), whi = lane_f(whi_l, li);
         const int p = first_px(g, v), off = p - sh;
         int lo = lo_of(v), hi = hi_of(v);
         // residue of this plane's row start
-        const int par = GEN ? (v & 1) : gpar;
+        const int par = GEN ? (row_par(v) & 1) : gpar;
         if (n == first_special || n == last_special) {
             // the readable extent [in - in_lo, in + in_hi), as window starts
             // of this row with the load's alignment
@@ -1069,7 +1085,7 @@ struct VecTile {
             run_projections();
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const int64_t o = (int64_t)r * W + xcol(g), rw = (int64_t)a.R * W;
+            const int64_t o = (int64_t)(r + lrow) * W + xcol(g), rw = (int64_t)a.R * W;
             if (a.psum)
                 *(f32x4_any *)bounded(a.psum + o, 4, a.psum, a.psum + rw) = f32x4{
                     (float)acc[g][0], (float)acc[g][1], (float)acc[g][2], (float)acc[g][3]};
@@ -1358,6 +1374,25 @@ __global__ __launch_bounds__(kSplitBlock) void k_forward_split(FwdArgs<TIn> a, i
         if (a.psum) *bounded(a.psum + o, 1, a.psum, a.psum + rw) = (float)acc;
         if (a.pmax) *bounded(a.pmax + o, 1, a.pmax, a.pmax + rw) = mx;
     }
+}
+
+// Projections of frames with short rows or of tiles that meet few planes: such
+// a launch is bound by instructions, most of them spent on planes that reach
+// few of a wavefront's 256 columns and on setting the wavefront up.  Here a
+// wavefront covers kProjectRows rows x 64 columns, which (C + 64) / s planes
+// reach instead of (C + 256) / s, with one set of coefficients for all rows.
+// 50x1304x87 into 3653 columns: 25.5 -> 18.6 us; 401x1209x130: 102 -> 60.
+constexpr int kProjectRows = 4;
+constexpr int kProjectPlanes = 2;
+
+template <typename TIn>
+__global__ __launch_bounds__(64, vec_waves_per_eu(1, kProjectPlanes, false, (int)sizeof(TIn))) void
+k_project_rows(FwdArgs<TIn> a, int tiles_x, int row_groups) {
+    const int k = (int)(blockIdx.x / (unsigned)row_groups);
+    const int rg = (int)blockIdx.x - k * row_groups;
+    VecTile<TIn, 64, 1, kProjectPlanes, false, false, true, true, kProjectRows> vt(
+        a, rg, middle_out(k, tiles_x), (int)threadIdx.x);
+    vt.run();
 }
 
 // Job record of the persistent ragged-batch kernel (device-resident table).

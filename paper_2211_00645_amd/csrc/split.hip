@@ -1,5 +1,6 @@
-// split.hip -- launches of the split kernel (frames of few tiles), in a
-// translation unit of its own.
+// split.hip -- launches of the split kernel (frames of few tiles) and of the
+// row kernel (projections whose tiles meet few planes), in a translation unit
+// of their own.
 #include <hip/hip_runtime.h>
 
 #include "common.hpp"
@@ -27,7 +28,21 @@ hipError_t launch(const FwdArgs<TIn> &a, int64_t tiles, hipStream_t s) {
     return a.N < 24 ? launch_planes<TIn, 2>(a, tiles, s) : launch_planes<TIn, 4>(a, tiles, s);
 }
 
+template <typename TIn>
+hipError_t project(const FwdArgs<TIn> &a, hipStream_t s) {
+    constexpr int64_t cols = 256 / kProjectRows;
+    const int64_t tiles = (a.W + cols - 1) / cols;
+    const int64_t groups = ((int64_t)a.R + kProjectRows - 1) / kProjectRows;
+    hipLaunchKernelGGL(k_project_rows<TIn>, dim3((unsigned)(tiles * groups)), dim3(64), 0, s, a,
+                       (int)tiles, (int)groups);
+    return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_project_rows(const FwdArgs<uint16_t> &a, hipStream_t s) { return project(a, s); }
+
+hipError_t launch_project_rows(const FwdArgs<float> &a, hipStream_t s) { return project(a, s); }
 
 hipError_t launch_split(const FwdArgs<uint16_t> &a, int64_t tiles, hipStream_t s) {
     return launch(a, tiles, s);
