@@ -303,7 +303,9 @@ int dsk_batch_destroy(dsk_batch *batch);
 /* Bytes of device job table dsk_jobs_launch needs for n_jobs jobs. */
 size_t dsk_jobs_table_bytes(int n_jobs);
 
-/* One persistent launch over jobs given per call (the serving path).
+/* Jobs given per call (the serving path) on `stream`: one persistent launch
+ * over all of them, except that with tune NULL a job with a volume that moves
+ * 400 MB or more goes out in a launch of its own.
  * table_host: host buffer of dsk_jobs_table_bytes(n_jobs) bytes, ideally
  * pinned; it is encoded here and, for lists of more than 32 jobs or a shape
  * other than the default's, copied to table_dev with hipMemcpyAsync on

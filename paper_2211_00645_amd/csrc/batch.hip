@@ -10,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -465,20 +466,13 @@ extern "C" size_t dsk_jobs_table_bytes(int n_jobs) {
     return n_jobs > 0 ? sizeof(JobDev) * (size_t)n_jobs : 0;
 }
 
-extern "C" int dsk_jobs_launch(const dsk_job *jobs, int n_jobs, void *table_host,
-                               void *table_dev, size_t table_bytes, const dsk_tune *tune,
-                               hipStream_t stream) {
-    if (!jobs || n_jobs <= 0 || !table_host || !table_dev) return DSK_EINVAL;
-    if (table_bytes < dsk_jobs_table_bytes(n_jobs)) return DSK_ESHAPE;
-    bool any_vol = false;
-    for (int i = 0; i < n_jobs; ++i) any_vol = any_vol || jobs[i].vol != nullptr;
-    dsk_tune t = tune ? *tune : (any_vol ? kDefaultTune : kDefaultProjTune);
-    if (!tune_ok(t)) return DSK_EINVAL;
-    for (int i = 0; i < n_jobs; ++i) {
-        const int st = validate_job(jobs[i]);
-        if (st != DSK_OK) return st;
-    }
-    if (!tune) {
+namespace {
+
+// One persistent launch over checked jobs.  own: the library's choice of
+// shape, paced only when every job has one frame.
+int launch_table(const dsk_job *jobs, int n_jobs, JobDev *host, void *table_dev, dsk_tune t,
+                 bool own, hipStream_t stream) {
+    if (own) {
         // wavefronts of different stacks cannot keep one schedule
         for (int i = 1; i < n_jobs; ++i) {
             const dsk_job &a = jobs[0], &b = jobs[i];
@@ -489,7 +483,6 @@ extern "C" int dsk_jobs_launch(const dsk_job *jobs, int n_jobs, void *table_host
             }
         }
     }
-    JobDev *host = (JobDev *)table_host;
     SubLaunch subs[2];
     hipError_t e = hipSuccess;
     const int ns = encode_table(jobs, n_jobs, t, host, subs);
@@ -497,11 +490,65 @@ extern "C" int dsk_jobs_launch(const dsk_job *jobs, int n_jobs, void *table_host
     const int st = plan_launches(t, host, subs, ns);
     if (st != DSK_OK) return st;
     // a short table travels in the launch's arguments: no copy before it
-    if (n_jobs <= kArgJobs && launch_jobs_by_value(host, subs, ns, t, stream, &e)) return hip_status(e);
+    if (n_jobs <= kArgJobs && launch_jobs_by_value(host, subs, ns, t, stream, &e))
+        return hip_status(e);
     e = hipMemcpyAsync(table_dev, host, dsk_jobs_table_bytes(n_jobs), hipMemcpyHostToDevice,
                        stream);
     if (e == hipSuccess) e = launch_jobs((const JobDev *)table_dev, subs, ns, t, stream);
     return hip_status(e);
+}
+
+// Bytes a job with a volume moves from which it goes out in a launch of its
+// own: its wavefronts then keep one plane schedule, which those of a launch
+// over several stacks cannot.  One launch over all jobs -> own launches, us:
+// 2 stacks of 529 and 983 MB 409 -> 273, 6 of 704-2788 MB 2736 -> 1952; 8 of
+// 28-421 MB 356 and 360, 8 of 15-215 MB 176 and 252.
+constexpr double kOwnLaunchBytes = 400e6;
+
+bool goes_alone(const dsk_job &j) {
+    return j.vol && (double)j.dims.planes * j.dims.rows *
+                            (2.0 * j.dims.cols + 4.0 * (double)j.out_width) >=
+                        kOwnLaunchBytes;
+}
+
+}  // namespace
+
+extern "C" int dsk_jobs_launch(const dsk_job *jobs, int n_jobs, void *table_host,
+                               void *table_dev, size_t table_bytes, const dsk_tune *tune,
+                               hipStream_t stream) {
+    if (!jobs || n_jobs <= 0 || !table_host || !table_dev) return DSK_EINVAL;
+    if (table_bytes < dsk_jobs_table_bytes(n_jobs)) return DSK_ESHAPE;
+    if (tune && !tune_ok(*tune)) return DSK_EINVAL;
+    for (int i = 0; i < n_jobs; ++i) {
+        const int st = validate_job(jobs[i]);
+        if (st != DSK_OK) return st;
+    }
+    JobDev *host = (JobDev *)table_host;
+    try {
+        if (tune) return launch_table(jobs, n_jobs, host, table_dev, *tune, false, stream);
+        std::vector<dsk_job> together;
+        together.reserve((size_t)n_jobs);
+        bool any_vol = false;
+        for (int i = 0; i < n_jobs; ++i) {
+            if (goes_alone(jobs[i])) continue;
+            together.push_back(jobs[i]);
+            any_vol = any_vol || jobs[i].vol != nullptr;
+        }
+        int st = DSK_OK;
+        if (!together.empty())
+            st = launch_table(together.data(), (int)together.size(), host, table_dev,
+                              any_vol ? kDefaultTune : kDefaultProjTune, true, stream);
+        for (int i = 0; i < n_jobs && st == DSK_OK; ++i) {
+            const dsk_job &j = jobs[i];
+            if (!goes_alone(j)) continue;
+            st = launch_forward_default(j.in, 0, j.dims, dense_layout(j.dims), j.offsets_dev,
+                                        j.shift_px, j.origin, j.vol, j.psum, j.pmax, j.out_width,
+                                        stream);
+        }
+        return st;
+    } catch (const std::bad_alloc &) {
+        return DSK_ENOMEM;
+    }
 }
 
 #if DSK_CHECK_BOUNDS

@@ -32,3 +32,21 @@ def test_job_lists(n_jobs, tune):
             for k in ("vol", "psum", "pmax"):
                 if k in out:
                     assert torch.equal(out[k], ref[k]), (tuple(st.shape), k)
+
+
+def test_large_and_small_stacks_together():
+    """Stacks that go out in launches of their own beside ones that share one."""
+    launcher = JobLauncher(max_jobs=4)
+    jobs, keep = [], []
+    for shape in ((9, 20, 61), (64, 512, 2048), (30, 31, 200)):
+        st = torch.randint(0, 65536, shape, dtype=torch.int32, device=DEV).to(torch.uint16)
+        job, out = plan_job(st, 35.0, 0.4, 0.115)
+        jobs.append(job)
+        keep.append((st, out))
+    assert keep[1][1]["vol"].numel() * 4 > 280e6
+    launcher.launch(jobs)
+    torch.cuda.synchronize()
+    for st, out in keep:
+        ref = dsk.deskew(st, 35.0, 0.4, 0.115)
+        for k in ("vol", "psum", "pmax"):
+            assert torch.equal(out[k], ref[k]), (tuple(st.shape), k)
