@@ -34,9 +34,10 @@ constexpr dsk_tune kDefaultTune = {64, 4, 1, 2, 0, 5700};
 // running wavefront back, it only makes the wavefronts whose plane range
 // starts late (the frame's outer column tiles) wait for their turn instead
 // of competing with the others at the start: 0.238 -> 0.219 ms on that
-// stack.  A frame with more tiles than resident workgroups is not paced
-// (fwd_launch): its second round of tiles would wait out a schedule that
-// began before they did (1-3% slower when they were).
+// stack.  With more tiles than resident workgroups a uniform scan's tiles go
+// out in the order in which they meet the planes; of other frames the second
+// round would wait out a schedule that began before it did (1-3% slower), so
+// they are not paced (fwd_launch_vec), nor are small stacks (default_tune).
 constexpr dsk_tune kDefaultProjTune = {64, 4, 1, 4, 0, 9000};
 
 inline bool dims_ok(dsk_dims d) {

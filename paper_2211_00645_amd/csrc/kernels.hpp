@@ -272,7 +272,8 @@ __device__ __forceinline__ void fwd_tile_scalar(const FwdArgs<TIn> &a, int r, in
 }
 
 // ---- vector variant ------------------------------------------------------
-// Preconditions (checked on the host): rows*W and the plane pitch are
+// Preconditions of the aligned form (vec_mode on the host; the general form,
+// GEN below, takes every other frame at least 4 columns wide): rows*W and the plane pitch are
 // multiples of 4, the stack is 8-byte (uint16) / 16-byte (float) aligned,
 // the volume 16-byte aligned.  Then the flat volume index of (n, r, x') is
 // 4-aligned exactly when x' + r*W is, independently of n, so a thread can
