@@ -20,6 +20,8 @@
 
 #include <type_traits>
 
+#include "window.hpp"
+
 namespace dsk {
 
 // How a frame is tiled (vec_mode in common.hpp): by the scalar kernel, by the
@@ -459,10 +461,9 @@ struct VecTile {
     using Win = RawWin<TIn>;
     const FwdArgs<TIn> &a;
     int r, W, C, N, ca, ng, wv, lane, gpar;
-    // window starts (elements from the row start) that keep a window of
-    // Win::kLen elements, with the load's alignment, inside the stack away
-    // from its two ends
-    int lo_off, hi_off;
+    // window starts that keep a window, with the load's alignment, inside the
+    // stack away from its two ends
+    WinRange near_row;
     int first_special, last_special;   // planes whose row lies at a stack end
     int64_t rstep, ostep;
     const TIn *rp0;                    // row r of plane 0
@@ -514,14 +515,13 @@ struct VecTile {
         constexpr int K = Win::kAlign;
         gpar = (int)(((int64_t)r * a.in_row +
                       (GEN ? (int64_t)((uintptr_t)a.in / sizeof(TIn)) : 0)) & (K - 1));
-        lo_off = -8 + ((K - (gpar + 8) % K) % K);
-        hi_off = C - 1 - ((C - 1 + gpar) & (K - 1));
+        near_row = row_windows<K>(C, gpar);
         // plane pitch >= 8: only plane 0 can start closer than 8 elements to
         // the readable start and only plane N-1 can end closer than 8 to its end
         const int64_t g0 = (int64_t)r * a.in_row;
-        first_special = (g0 - 8 < -a.in_lo) ? 0 : -1;
+        first_special = near_first(g0, a.in_lo) ? 0 : -1;
         const int64_t g1 = ROWS > 1 ? (int64_t)min(r + ROWS - 1, a.R - 1) * a.in_row : g0;
-        last_special = ((int64_t)(N - 1) * rstep + g1 + C + 8 > a.in_hi) ? N - 1 : -1;
+        last_special = near_last((int64_t)(N - 1) * rstep + g1, C, a.in_hi) ? N - 1 : -1;
         rp0 = a.in + (int64_t)r * a.in_row;
         op0 = VOL ? a.vol + (int64_t)r * W : nullptr;
         tau = a.tau256;
@@ -568,12 +568,9 @@ struct VecTile {
     // Parity of the row start of the lane's row (GEN: in a plane of packed v).
     __device__ __forceinline__ int row_par(int v) const { return ROWS > 1 ? v + lelem : v; }
 
-    // lo_off and hi_off of a plane (GEN: with its row start's parity)
-    __device__ __forceinline__ int lo_of(int v) const {
-        return GEN && Win::kAlign == 2 ? -8 + (row_par(v) & 1) : lo_off;
-    }
-    __device__ __forceinline__ int hi_of(int v) const {
-        return GEN && Win::kAlign == 2 ? C - 1 - ((C - 1 + row_par(v)) & 1) : hi_off;
+    // near_row of a plane (GEN: with its row start's parity)
+    __device__ __forceinline__ WinRange windows(int v) const {
+        return GEN && Win::kAlign == 2 ? row_windows<2>(C, row_par(v)) : near_row;
     }
 
     __device__ __forceinline__ int xcol(int g) const { return ca + gx[g]; }
@@ -657,10 +654,7 @@ struct VecTile {
     __device__ __forceinline__ void fetch(int g, const TIn *rp, int v, Win &w) const {
         int off = (v >> 1) + gx[g];
         if constexpr (GEN) off -= win_shift(g, v);
-        if (MASK) {
-            const int lo = lo_of(v), hi = hi_of(v);
-            off = off < lo ? lo : (off > hi ? hi : off);
-        }
+        if (MASK) off = clamp_start(off, windows(v));
         if constexpr (ROWS > 1) off += lelem;
         w.load(bounded(rp + off, Win::kLen, a.in - a.in_lo, a.in + a.in_hi));
     }
@@ -697,20 +691,12 @@ struct VecTile {
         const int sh = win_shift(g, v);
         const float wlo = lane_f(wlo_l, li), whi = lane_f(whi_l, li);
         const int p = first_px(g, v), off = p - sh;
-        int lo = lo_of(v), hi = hi_of(v);
+        WinRange wr = windows(v);
         // residue of this plane's row start
         const int par = GEN ? (row_par(v) & 1) : gpar;
-        if (n == first_special || n == last_special) {
-            // the readable extent [in - in_lo, in + in_hi), as window starts
-            // of this row with the load's alignment
-            const int64_t grow = rp - a.in;
-            int64_t lo_ok = -grow - a.in_lo, hi_ok = a.in_hi - Win::kLen - grow;
-            lo_ok += (par + lo_ok) & (K - 1);
-            hi_ok -= (par + hi_ok) & (K - 1);
-            lo = (int)(lo_ok > (int64_t)lo ? lo_ok : (int64_t)lo);
-            hi = (int)(hi_ok < (int64_t)hi ? hi_ok : (int64_t)hi);
-        }
-        const int oc = off < lo ? lo : (off > hi ? hi : off);
+        if (n == first_special || n == last_special)
+            wr = end_windows<K, Win::kLen>(wr, rp - a.in, a.in_lo, a.in_hi, par);
+        const int oc = clamp_start(off, wr);
         Win raw;
         raw.load(bounded(rp + oc, Win::kLen, a.in - a.in_lo, a.in + a.in_hi));
         float vv[5];
@@ -737,15 +723,11 @@ struct VecTile {
     // end, to the readable extent (at any element there: an aligned window
     // may not reach the extent's last one).
     __device__ __forceinline__ int exact_off(int n, int v) const {
-        int lo = lo_of(v), hi = hi_of(v);
-        if (n == first_special || n == last_special) {
-            const int64_t grow = (int64_t)r * a.in_row + (int64_t)n * rstep;
-            const int64_t lo_ok = -grow - a.in_lo, hi_ok = a.in_hi - Win::kLen - grow;
-            lo = (int)(lo_ok > (int64_t)lo ? lo_ok : (int64_t)lo);
-            hi = (int)(hi_ok < (int64_t)hi ? hi_ok : (int64_t)hi);
-        }
-        const int off = first_px(0, v) - win_shift(0, v);
-        return off < lo ? lo : (off > hi ? hi : off);
+        WinRange wr = windows(v);
+        if (n == first_special || n == last_special)
+            wr = end_windows<1, Win::kLen>(wr, (int64_t)r * a.in_row + (int64_t)n * rstep,
+                                           a.in_lo, a.in_hi, 0);
+        return clamp_start(first_px(0, v) - win_shift(0, v), wr);
     }
 
     // Interpolate group 0 of plane n from its window at exact_off(n, v).
