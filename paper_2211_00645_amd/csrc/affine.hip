@@ -14,7 +14,8 @@
 // that each voxel's weights, which depend on (y, z) only, serve four voxels.
 // The one-shot kernel (k_affine, one lane per 4 output columns in output
 // order) covers the geometries whose images no ring holds (grids as coarse as
-// the scan, very fine scans) and rows of one column.
+// the scan, |uy| = dy / s_z of 0.9994 and more; very fine scans) and rows of
+// one column.
 //
 // Bound: writes to HBM in this output order (a kernel of the same stores and
 // nothing else: 2.70 ms on the 512x512x2048 stack, 5.4 TB/s).  Measured:
@@ -31,6 +32,7 @@
 #include "common.hpp"
 #include "deskew.h"
 #include "kernels.hpp"
+#include "strip.hpp"
 
 using namespace dsk;
 
@@ -126,14 +128,7 @@ __global__ __launch_bounds__(kAffBlock) void k_affine(AffArgs<TIn> a) {
 // Loads take 2 pixels at any 2-byte boundary and a row's partial groups are
 // stored by column, so any column count of at least 2 and any row phase runs
 // here.
-constexpr int kStripRows = 4;
-constexpr int kStripCols = 64;
-constexpr int kRing = 64;
-constexpr int kNewImages = 16;
 constexpr int kStripBlock = 256;
-constexpr int kChunk = 16;
-
-constexpr int strip_window(bool phase) { return kStripCols + (phase ? 32 : 0); }
 
 // 32 KB of LDS each, 48 KB with the wider window
 constexpr int strip_wg_per_cu(bool phase) { return phase ? 3 : 4; }
@@ -407,13 +402,7 @@ extern "C" int dsk_affine_u16(const uint16_t *in, dsk_dims d, dsk_geom g, double
                           a.u0 + (double)(ny - 1) * a.uy - (double)(d.cols - 1) * a.uz};
     bool u_ok = true;
     for (double v : ue) u_ok = u_ok && std::fabs(v) < 1.0e9;
-    // The images a chunk adds fit the loads of one chunk and its band the
-    // ring (2 images besides the span, one for rounding).
-    auto fits = [&](bool phase) {
-        return kChunk * std::fabs(a.uy) + 1.0 <= kNewImages &&
-               (strip_window(phase) - 1) * std::fabs(a.uz) + kChunk * std::fabs(a.uy) + 3.0 <=
-                   kRing;
-    };
+    auto fits = [&](bool phase) { return strip_fits(a.uy, a.uz, phase); };
     // Outputs the last-level cache holds: it joins partial lines, and plain
     // stores let it (28x667x135, 74 MB: 35 us with whole lines streamed past
     // it, 22 so).  Larger ones are streamed in whole lines.

@@ -64,3 +64,17 @@ def test_large_outputs(shape, ang, step, dy):
     assert 4 * ny * shape[1] * shape[2] > 256000000
     _check(shape, ang, step, dy, rows=[*range(0, 40), *range(250, 290), ny // 2,
                                        *range(ny - 40, ny)])
+
+
+@pytest.mark.parametrize("shape,ang,step,dy", [
+    ((70, 5, 129), 35.0, 0.4, 0.38),          # 15.2 images a chunk
+    ((70, 3, 200), 30.0, 0.4, 0.3996),        # 15.98
+    ((70, 3, 66), 60.0, -0.4, 0.399),         # reversed
+    ((600, 330, 301), 45.0, 0.38, 0.38 * 0.999),   # rows of one phase apart
+])
+@pytest.mark.parametrize("off", [0, 1])
+def test_steps_nearly_as_coarse_as_the_scan(shape, ang, step, dy, off):
+    """Up to 16 new images a chunk of 16 y values."""
+    _, ny = dsk.affine_plan(shape, ang, step, 0.115, dy)
+    rows = None if ny < 200 else [*range(0, 40), ny // 2, *range(ny - 40, ny)]
+    _check(shape, ang, step, dy, rows=rows, off=off)
