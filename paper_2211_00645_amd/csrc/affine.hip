@@ -299,7 +299,7 @@ __global__ __launch_bounds__(kStripBlock, strip_wg_per_cu(PHASE)) void k_affine_
                 if (zq >= 0 && zq + 4 <= a.C) {
 #pragma unroll
                     for (int r = 0; r < NR; ++r)
-                        if (rok[r]) store_f32x4<NT, f32x4_any>(o + orow[r], v[r]);
+                        if (rok[r]) store_f32x4<NT, true>(o + orow[r], v[r]);
                 } else {
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {

@@ -20,6 +20,7 @@
 
 #include <type_traits>
 
+#include "quad.hpp"
 #include "window.hpp"
 
 namespace dsk {
@@ -284,18 +285,6 @@ __device__ __forceinline__ void fwd_tile_scalar(const FwdArgs<TIn> &a, int r, in
 // reach that alignment.  A group's 5 source pixels come from one load: 12
 // bytes from a dword-aligned uint16 element (then a 0- or 16-bit funnel shift
 // that is the same for the whole wavefront), or 16 + 4 bytes of float.
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-// the same 16 bytes at any 4-byte boundary (one instruction on gfx950)
-typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-
-template <bool NT, typename V = f32x4>
-__device__ __forceinline__ void store_f32x4(float *p, f32x4 v) {
-    if constexpr (NT)
-        __builtin_nontemporal_store((V)v, (V *)p);
-    else
-        *(V *)p = v;
-}
 
 // Raw source window of one 4-column group.  uint16: the 6 pixels (12 bytes)
 // starting at the even element at or one before the first needed pixel;
@@ -759,7 +748,7 @@ struct VecTile {
     // ---- with a volume ---------------------------------------------------
 
     __device__ __forceinline__ void store(int g, float *orow, const float d[4]) const {
-        store_f32x4<NT, std::conditional_t<GEN, f32x4_any, f32x4>>(
+        store_f32x4<NT, GEN>(
             bounded(orow + xcol(g), 4, a.vol, a.vol + (int64_t)N * a.vol_plane),
             f32x4{d[0], d[1], d[2], d[3]});
     }
@@ -1552,7 +1541,7 @@ __global__ __launch_bounds__(BLOCK) void k_backward(BwdArgs a) {
                 o.y = fmaf(pc.whi, gv[1], pc.wlo * gv[2]);
                 o.z = fmaf(pc.whi, gv[2], pc.wlo * gv[3]);
                 o.w = fmaf(pc.whi, gv[3], pc.wlo * gv[4]);
-                store_f32x4<true, f32x4_any>(
+                store_f32x4<true, true>(
                     bounded(a.gin + rowi * C + c, 4, a.gin, a.gin + nr * C), o);
             }
             if constexpr (GOFF) {
@@ -1657,7 +1646,7 @@ __device__ __forceinline__ float roll_px(const RollArgs &a, const PlaneCoef &pc,
     return fmaf(pc.whi, load_px(row, i, (int64_t)a.C), pc.wlo * load_px(row, i - 1, (int64_t)a.C));
 }
 
-// Walks V pixels (V = f32x4_any, or float for the last pixels) from leaf n,
+// Walks V pixels (V = f32x4, or float for the last pixels) from leaf n,
 // at plane offset idx, to the root, refreshing every node; the root's value.
 template <typename V>
 __device__ __forceinline__ V roll_path(const RollArgs &a, int64_t idx, int64_t RW, V m) {
@@ -1667,12 +1656,12 @@ __device__ __forceinline__ V roll_path(const RollArgs &a, int64_t idx, int64_t R
     for (int l = 0; l < a.levels; ++l) {
         const int sib = j ^ 1;
         if (sib < cnt) {
-            const V b = *(const V *)(below + (int64_t)sib * RW + idx);
+            const V b = load_any<V>(below + (int64_t)sib * RW + idx);
             m = __builtin_elementwise_max(m, b);
         }
         j >>= 1;
         const int next = (cnt + 1) >> 1;
-        *(V *)(lev + (int64_t)j * RW + idx) = m;
+        store_any(lev + (int64_t)j * RW + idx, m);
         below = lev;
         lev += (int64_t)next * RW;
         cnt = next;
@@ -1729,7 +1718,7 @@ __global__ __launch_bounds__(256) void k_rolling_update(RollArgs a) {
     const f32x4 old = *(const f32x4_any *)leaf;
     f64x2_any s01 = *(const f64x2_any *)(a.sum64 + idx);
     f64x2_any s23 = *(const f64x2_any *)(a.sum64 + idx + 2);
-    f32x4_any m = f32x4{d[0], d[1], d[2], d[3]};
+    f32x4 m = f32x4{d[0], d[1], d[2], d[3]};
     bool same = true;
 #pragma unroll
     for (int e = 0; e < 4; ++e) same = same && __float_as_int(d[e]) == __float_as_int(old[e]);
@@ -1741,7 +1730,7 @@ __global__ __launch_bounds__(256) void k_rolling_update(RollArgs a) {
         s23.y = s23.y + ((double)d[3] - (double)old.w);
         *(f64x2_any *)(a.sum64 + idx) = s01;
         *(f64x2_any *)(a.sum64 + idx + 2) = s23;
-        m = roll_path<f32x4_any>(a, idx, RW, m);
+        m = roll_path<f32x4>(a, idx, RW, m);
     } else if (a.levels) {
         m = *(const f32x4_any *)root;
     }
