@@ -177,9 +177,11 @@ int dsk_deskew_offsets_tuned(const void *in, int in_is_f32, dsk_dims d,
  * outputs may be written (with the correct values) or, when the choice is
  * already known, left untouched: call the forward with *tune afterwards.
  * The choice is remembered per architecture, input type, dims, out_width,
- * output set and offsets/uniform scan, in the process and, if the
+ * output set, offsets/uniform scan and how the buffers' alignment lets them
+ * tile, in the process and, with the kernels' revision, if the
  * environment variable DSK_TUNE_CACHE names a file, in that JSON file; a
- * remembered choice returns at once without launching.  Synchronises the
+ * remembered choice returns at once without launching (under stream capture
+ * one of another alignment serves).  Synchronises the
  * stream while timing.  Errors of the arguments are those of the forward. */
 int dsk_deskew_autotune(const void *in, int in_is_f32, dsk_dims d,
                         const double *offsets_dev, double shift_px,

@@ -213,8 +213,8 @@ bool launch_jobs_by_value(const JobDev *table, const SubLaunch *subs, int ns, co
 
 int log2_bucket(double v) { return v <= 1.0 ? 0 : (int)std::floor(std::log2(v)); }
 
-// Shape class: arch, job count, and log2 buckets of total output voxels
-// and mean planes per job.
+// Shape class: arch, kernel revision, job count, and log2 buckets of total
+// output voxels and mean planes per job.
 std::string shape_key(const dsk_job *jobs, int n) {
     double vox = 0.0, planes = 0.0;
     for (int i = 0; i < n; ++i) {
@@ -222,8 +222,8 @@ std::string shape_key(const dsk_job *jobs, int n) {
         planes += jobs[i].dims.planes;
     }
     char buf[160];
-    std::snprintf(buf, sizeof buf, "%s/jobs%d/vox2^%d/planes2^%d", arch_name().c_str(), n,
-                  log2_bucket(vox), log2_bucket(planes / n));
+    std::snprintf(buf, sizeof buf, "%s/k%d/jobs%d/vox2^%d/planes2^%d", arch_name().c_str(),
+                  kTuneRevision, n, log2_bucket(vox), log2_bucket(planes / n));
     return buf;
 }
 

@@ -159,6 +159,11 @@ int batch_bounds_violations(unsigned long long *count, bool reset);
 int split_bounds_violations(unsigned long long *count, bool reset);
 #endif
 
+// How a dense stack and its volume tile in the default shape: "lines" (aligned,
+// on 128-byte boundaries of the volume), "aligned", "general" or "scalar".
+const char *tiling_name(const void *in, int in_is_f32, dsk_dims d, const float *vol,
+                        int64_t width);
+
 // The same without a launch shape: the library's choice for the frame.
 int launch_forward_default(const void *in, int in_is_f32, dsk_dims d, const InLayout &lay,
                            const double *offs, double shift, int64_t origin, float *vol,

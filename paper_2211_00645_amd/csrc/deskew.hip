@@ -237,6 +237,15 @@ static bool tiles_aligned(const float *vol, dsk_dims d, int64_t width, const dsk
                tiles_x(width, t, vec);
 }
 
+const char *tiling_name(const void *in, int in_is_f32, dsk_dims d, const float *vol,
+                        int64_t width) {
+    const dsk_tune &t = vol ? kDefaultTune : kDefaultProjTune;
+    const int vec = vec_mode(t, d, width, in, in_is_f32, vol, (int64_t)d.rows * d.cols);
+    if (vec == VEC_NONE) return "scalar";
+    if (vec == VEC_GENERAL) return "general";
+    return tiles_aligned(vol, d, width, t, vec) ? "lines" : "aligned";
+}
+
 // kDefaultTune (or kDefaultProjTune without a volume) with the pace and the
 // pipeline depth that hold for the frame.  GB/s measured over frames of
 // 100-1304 rows, 256-2048 columns and 16-400 planes:

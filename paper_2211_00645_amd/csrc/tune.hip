@@ -145,12 +145,16 @@ std::vector<dsk_tune> fwd_candidates(bool paced) {
     return c;
 }
 
-std::string fwd_key(int in_is_f32, dsk_dims d, int64_t width, bool offs, const float *vol,
-                    const float *psum, const float *pmax) {
+// How the buffers tile is part of the key: it decides which vector kernel runs
+// and where its pace's cliff lies (default_tune in deskew.hip: 5700 GB/s on
+// 128-byte boundaries is past it elsewhere).
+std::string fwd_key(const char *tiling, int in_is_f32, dsk_dims d, int64_t width, bool offs,
+                    const float *vol, const float *psum, const float *pmax) {
     char buf[200];
-    std::snprintf(buf, sizeof buf, "%s/fwd/%s/%dx%dx%d/w%lld/%s%s%s/%s", arch_name().c_str(),
-                  in_is_f32 ? "f32" : "u16", d.planes, d.rows, d.cols, (long long)width,
-                  vol ? "v" : "", psum ? "s" : "", pmax ? "m" : "", offs ? "offsets" : "uniform");
+    std::snprintf(buf, sizeof buf, "%s/k%d/fwd/%s/%dx%dx%d/w%lld/%s/%s%s%s/%s",
+                  arch_name().c_str(), kTuneRevision, in_is_f32 ? "f32" : "u16", d.planes, d.rows,
+                  d.cols, (long long)width, tiling, vol ? "v" : "", psum ? "s" : "",
+                  pmax ? "m" : "", offs ? "offsets" : "uniform");
     return buf;
 }
 
@@ -308,17 +312,26 @@ extern "C" int dsk_deskew_autotune(const void *in, int in_is_f32, dsk_dims d,
     if (!tune || out_width <= 0 || reps < 3 || reps > 64) return DSK_EINVAL;
     if (!in || !dims_ok(d) || (!vol && !psum && !pmax)) return DSK_EINVAL;
     if (!offsets_dev && !std::isfinite(shift_px)) return DSK_EINVAL;
-    const std::string key =
-        fwd_key(in_is_f32, d, out_width, offsets_dev != nullptr, vol, psum, pmax);
-    {
+    auto key_of = [&](const char *tiling) {
+        return fwd_key(tiling, in_is_f32 ? 1 : 0, d, out_width, offsets_dev != nullptr, vol, psum,
+                       pmax);
+    };
+    const std::string key = key_of(tiling_name(in, in_is_f32 ? 1 : 0, d, vol, out_width));
+    auto remembered = [&](const std::string &k) {
         std::lock_guard<std::mutex> lk(g_memo_mu);
-        auto it = g_memo.find(key);
-        if (it != g_memo.end()) {
-            *tune = it->second.first;
-            if (ms) *ms = it->second.second;
-            return DSK_OK;
-        }
-    }
+        auto it = g_memo.find(k);
+        if (it == g_memo.end()) return false;
+        *tune = it->second.first;
+        if (ms) *ms = it->second.second;
+        return true;
+    };
+    if (remembered(key)) return DSK_OK;
+    // a stream under capture cannot be timed: there the shape that another
+    // tiling of the frame was given serves
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
+        for (const char *tiling : {"lines", "aligned", "general", "scalar"})
+            if (remembered(key_of(tiling))) return DSK_OK;
     dsk_tune best{};
     double best_ms = 0.0;
     if (!tune_cache_lookup(key, &best, &best_ms, nullptr)) {
