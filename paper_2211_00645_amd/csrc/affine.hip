@@ -157,10 +157,8 @@ __global__ __launch_bounds__(kStripBlock, strip_wg_per_cu(PHASE)) void k_affine_
     __shared__ __align__(16) uint32_t ring[kRing * kSlot];
     const AffArgs<uint16_t> &a = sa.a;
     const int tid = (int)threadIdx.x, lane = tid & 63;
-    // neighbouring strips of a row on one XCD, whose L2 joins the lines they
-    // share
-    const int64_t bid = xcd_remap(blockIdx.x, gridDim.x);
-    const int64_t yc = bid / sa.strips, st = bid - yc * sa.strips;
+    const StripPlace at = strip_of_block(blockIdx.x, sa.strips);
+    const int64_t yc = at.part, st = at.strip;
     const int xi = (int)(st / sa.ztiles);
     const int S = PHASE ? sa.phase_rows : 1;
     const int x0 = xi / S * (NR * S) + xi % S;

@@ -22,6 +22,7 @@
 
 #include "quad.hpp"
 #include "window.hpp"
+#include "xcd.hpp"
 
 namespace dsk {
 
@@ -215,17 +216,6 @@ __device__ __forceinline__ void pace_until(uint64_t t0, uint32_t tau256, int n) 
         if (pace_clock() >= target) break;
         __builtin_amdgcn_s_sleep(2);
     }
-}
-
-// Spread consecutive workgroup ids, which the dispatcher deals round-robin
-// to the 8 XCDs, so that each XCD receives a contiguous range of logical
-// tiles (neighbouring tiles of a row then share that XCD's L2).  A
-// bijection on [0, n).
-__device__ __forceinline__ int64_t xcd_remap(int64_t b, int64_t n) {
-    constexpr int64_t kXcd = 8;
-    const int64_t q = n / kXcd, rem = n % kXcd;
-    const int64_t x = b % kXcd, i = b / kXcd;
-    return x * q + (x < rem ? x : rem) + i;
 }
 
 // ---- scalar variant: any alignment --------------------------------------

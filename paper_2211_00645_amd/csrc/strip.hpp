@@ -1,9 +1,12 @@
-// strip.hpp -- sizes of the affine strip kernel and the rule for the grids it
-// takes (affine.hip).  Plain C++, so that the rule can be checked without a
-// device.
+// strip.hpp -- sizes of the affine strip kernel, the rule for the grids it
+// takes and the order of its workgroups (affine.hip).  Plain C++ besides the
+// function qualifiers, so that they can be checked without a device.
 #pragma once
 
 #include <math.h>
+#include <stdint.h>
+
+#include "xcd.hpp"
 
 namespace dsk {
 
@@ -30,6 +33,24 @@ inline bool strip_fits(double uy, double uz, bool phase) {
     const double move = kChunk * fabs(uy);
     return move + 0.01 <= kNewImages &&
            (strip_window(phase) - 1) * fabs(uz) + move + 3.0 <= kRing;
+}
+
+// Part of the y range and strip of workgroup b.  The parts go out one after
+// another, so that the chip writes neighbouring planes at any time; within a
+// part each XCD has a contiguous range of strips, neighbours of a row, whose
+// shared lines its L2 joins.  One range per XCD over all parts had the 8 XCDs
+// write 8 parts at once: us over three outputs in turn, so -> now,
+// 256x256x1000 (1.7 GB, 7 parts) 494 -> 433, 256x512x1024 877 -> 782,
+// 200x301x777 522 -> 479, 70x512x448 into 743 (0.7 GB) 140.6 -> 138.2,
+// 300x40x1024 (0.3 GB) 65.1 -> 60.5; without the XCDs' ranges 424, 827, 458,
+// 137.3 and 60.0.
+struct StripPlace {
+    int64_t part, strip;
+};
+
+__host__ __device__ __forceinline__ StripPlace strip_of_block(int64_t b, int64_t strips) {
+    const int64_t part = b / strips;
+    return StripPlace{part, xcd_remap(b - part * strips, strips)};
 }
 
 }  // namespace dsk

@@ -1,8 +1,10 @@
-"""The rule for the grids of the affine strip kernel (csrc/strip.hpp), compiled
-for the host: it takes scan steps up to 0.999 images per y value, and on every
+"""The rules of the affine strip kernel (csrc/strip.hpp), compiled for the host.
+Grids: it takes scan steps up to 0.999 images per y value, and on every
 grid it takes the kernel's bookkeeping -- the last image of a chunk against
 that of the one before, the band against the ring -- stays within the loads of
-a chunk and the ring, in 64-bit arithmetic as on the device."""
+a chunk and the ring, in 64-bit arithmetic as on the device.  Workgroups: the
+parts of the y range in order, each strip of a part once, an XCD's workgroups
+of a part on neighbouring strips."""
 import os
 import subprocess
 
@@ -13,7 +15,9 @@ SRC = r"""
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
+#include <initializer_list>
 #include <random>
+#include <vector>
 #include "strip.hpp"
 using namespace dsk;
 
@@ -59,6 +63,20 @@ int main() {
             have = next;
         }
     }
+    for (int64_t strips : {1, 2, 7, 8, 9, 176, 1001, 4096})
+        for (int64_t parts : {1, 2, 5}) {
+            std::vector<int> seen(strips * parts, 0);
+            for (int64_t b = 0; b < strips * parts; ++b) {
+                const StripPlace p = strip_of_block(b, strips);
+                need(p.part == b / strips, "part out of order", (double)b, (double)strips);
+                need(p.strip >= 0 && p.strip < strips && !seen[p.part * strips + p.strip]++,
+                     "strip", (double)b, (double)strips);
+                // the next workgroup on this XCD
+                if (b + 8 < (p.part + 1) * strips)
+                    need(strip_of_block(b + 8, strips).strip == p.strip + 1, "neighbour",
+                         (double)b, (double)strips);
+            }
+        }
     std::printf("grids %ld bad %d\n", grids, bad);
     return bad != 0 || grids < 10000;
 }
@@ -68,7 +86,8 @@ int main() {
 def test_strip_rule(tmp_path):
     src, exe = tmp_path / "strip.cpp", tmp_path / "strip"
     src.write_text(SRC)
-    subprocess.run(["g++", "-std=c++17", "-O1", "-ffp-contract=off", "-I", CSRC, str(src), "-o",
+    subprocess.run(["g++", "-std=c++17", "-O1", "-ffp-contract=off", "-D__host__=",
+                    "-D__device__=", "-D__forceinline__=inline", "-I", CSRC, str(src), "-o",
                     str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout
