@@ -133,8 +133,6 @@ constexpr int kStripBlock = 256;
 // 32 KB of LDS each, 48 KB with the wider window
 constexpr int strip_wg_per_cu(bool phase) { return phase ? 3 : 4; }
 
-constexpr int64_t kCachedBytes = 256000000;
-
 struct StripArgs {
     AffArgs<uint16_t> a;
     int64_t ylen;        // y values per workgroup
@@ -401,12 +399,10 @@ extern "C" int dsk_affine_u16(const uint16_t *in, dsk_dims d, dsk_geom g, double
     bool u_ok = true;
     for (double v : ue) u_ok = u_ok && std::fabs(v) < 1.0e9;
     auto fits = [&](bool phase) { return strip_fits(a.uy, a.uz, phase); };
-    // Outputs the last-level cache holds: it joins partial lines, and plain
-    // stores let it (28x667x135, 74 MB: 35 us with whole lines streamed past
-    // it, 22 so).  Larger ones are streamed in whole lines.
-    const bool small = 4 * ny * d.rows * (int64_t)d.cols <= kCachedBytes;
-    const bool lines = ((uintptr_t)vol & 127) == 0 && d.cols % 32 == 0;
-    const bool phase = !small && !lines && fits(true);
+    const StripStores stores =
+        strip_stores(4 * ny * d.rows * (int64_t)d.cols,
+                     ((uintptr_t)vol & 127) == 0 && d.cols % 32 == 0, fits(true));
+    const bool phase = stores == StripStores::kPhase;
     if (u_ok && fits(phase) && d.cols >= 2 && ny < (int64_t(1) << 30) && ((uintptr_t)in & 1) == 0 &&
         ((uintptr_t)vol & 3) == 0) {
         int s = 1;   // rows s apart start at one place of a 128-byte line
@@ -425,7 +421,7 @@ extern "C" int dsk_affine_u16(const uint16_t *in, dsk_dims d, dsk_geom g, double
             };
             if (phase)
                 go(k_affine_strip<true, true>);
-            else if (lines && !small)
+            else if (stores == StripStores::kLines)
                 go(k_affine_strip<false, true>);
             else
                 go(k_affine_strip<false, false>);

@@ -35,6 +35,28 @@ inline bool strip_fits(double uy, double uz, bool phase) {
            (strip_window(phase) - 1) * fabs(uz) + move + 3.0 <= kRing;
 }
 
+// How the output is written.  Whole lines (the volume on 128-byte boundaries,
+// columns a multiple of 32) are streamed past the caches at any size.  Other
+// rows leave partial lines at both ends of a strip's run: outputs of up to
+// kCachedBytes go out in plain stores, whose partial lines the last-level cache
+// joins; larger ones are streamed in runs that start at line boundaries
+// (phase), or in plain stores where the ring does not hold the wider window.
+// us, streamed -> plain, over three and over eight outputs in turn:
+//   whole lines 40x64x256 into 345 (23 MB) 7.9 -> 8.6, 7.4 -> 8.8; 246x64x704
+//     (215 MB) 48.1 -> 62.4; 200x100x512 (228 MB) 47.0 -> 54.9 (over one output
+//     again and again 46.9 -> 39.5)
+//   other rows 28x667x135 (73 MB) 34.3 -> 19.5, 34.4 -> 30.2; 200x64x333 (82 MB)
+//     37.4 -> 21.1, 37.4 -> 35.6; 200x120x420 (209 MB) 50.0 -> 76.0, 49.1 -> 75.7;
+//     200x99x510 (224 MB) 61.2 -> 88.5 (one output 63.0 -> 49.3)
+enum class StripStores { kPlain, kLines, kPhase };
+
+constexpr int64_t kCachedBytes = 100000000;
+
+inline StripStores strip_stores(int64_t out_bytes, bool whole_lines, bool phase_fits) {
+    if (whole_lines) return StripStores::kLines;
+    return out_bytes > kCachedBytes && phase_fits ? StripStores::kPhase : StripStores::kPlain;
+}
+
 // Part of the y range and strip of workgroup b.  The parts go out one after
 // another, so that the chip writes neighbouring planes at any time; within a
 // part each XCD has a contiguous range of strips, neighbours of a row, whose

@@ -4,7 +4,7 @@ grid it takes the kernel's bookkeeping -- the last image of a chunk against
 that of the one before, the band against the ring -- stays within the loads of
 a chunk and the ring, in 64-bit arithmetic as on the device.  Workgroups: the
 parts of the y range in order, each strip of a part once, an XCD's workgroups
-of a part on neighbouring strips."""
+of a part on neighbouring strips.  Stores: whole lines streamed at any size."""
 import os
 import subprocess
 
@@ -63,6 +63,13 @@ int main() {
             have = next;
         }
     }
+    // whole lines are streamed at any size; other rows by the output's size
+    for (int64_t bytes : {1000ll, 215000000ll, 4000000000ll})
+        for (bool fits : {false, true}) {
+            need(strip_stores(bytes, true, fits) == StripStores::kLines, "lines", bytes, fits);
+            need((strip_stores(bytes, false, fits) == StripStores::kPhase) ==
+                     (fits && bytes > 200000000), "other rows", bytes, fits);
+        }
     for (int64_t strips : {1, 2, 7, 8, 9, 176, 1001, 4096})
         for (int64_t parts : {1, 2, 5}) {
             std::vector<int> seen(strips * parts, 0);
