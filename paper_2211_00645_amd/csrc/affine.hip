@@ -324,21 +324,20 @@ __global__ __launch_bounds__(kStripBlock, strip_wg_per_cu(PHASE)) void k_affine_
 
 // y values per workgroup.  Workgroups drift apart in y as they sweep, which
 // scatters the writes, so where the last-level cache holds the stack the y
-// range is cut into parts of at most kPartY values (every part loads its first
-// band anew): 200x301x777 0.404 -> 0.364 ms, 256x256x1000 0.633 -> 0.590,
-// 256x512x1024 (268 MB) 0.636 -> 0.609; from HBM the bands cost more than the
-// drift, and a larger stack is swept whole (512x512x2048, 1.07 GB: 3.23 ms,
-// in parts of 256 3.62).  With fewer than 4 rounds of resident workgroups
-// the range is cut further, into the count of parts that fills the rounds
-// best; a part costs its y values and about 24 more.
-constexpr int64_t kPartY = 256;
+// range is cut into parts of at most part_y values (strip_part; every part loads
+// its first band anew); from HBM the bands cost more than the drift, and a larger
+// stack is swept whole (512x512x2048, 1.07 GB: 3.23 ms, in parts of 256 3.62).
+// With fewer than 4 rounds of resident workgroups the range is cut further, into
+// the count of parts that fills the rounds best; a part costs its y values and
+// about 24 more.
 constexpr int64_t kCachedStack = 300000000;
 
-int64_t strip_ylen(int64_t strips, int64_t ny, int wg_per_cu, int64_t stack_bytes) {
+int64_t strip_ylen(int64_t strips, int64_t ny, int wg_per_cu, int64_t stack_bytes,
+                   int64_t part_y) {
     const int64_t resident = (int64_t)wg_per_cu * device_cus();
-    const int64_t first = stack_bytes <= kCachedStack ? (ny + kPartY - 1) / kPartY : 1;
+    const int64_t first = stack_bytes <= kCachedStack ? (ny + part_y - 1) / part_y : 1;
     int64_t best = first;
-    if (strips * first >= 4 * resident) return first == 1 ? ny : kPartY;
+    if (strips * first >= 4 * resident) return first == 1 ? ny : part_y;
     double cost = 1e300;
     for (int64_t parts = first;
          parts < first + 32 && (parts == first || ny / parts >= 2 * kChunk); ++parts) {
@@ -412,7 +411,8 @@ extern "C" int dsk_affine_u16(const uint16_t *in, dsk_dims d, dsk_geom g, double
         const int64_t per_class = ((int64_t)d.rows + s - 1) / s;
         const int64_t strips = s * ((per_class + kStripRows - 1) / kStripRows) * ztiles;
         const int64_t ylen = strip_ylen(strips, ny, strip_wg_per_cu(phase),
-                                        2 * (int64_t)d.planes * plane_px);
+                                        2 * (int64_t)d.planes * plane_px,
+                                        strip_part(stores, 4 * ny * plane_px, a.uy, a.uz));
         const int64_t blocks = strips * ((ny + ylen - 1) / ylen);
         if (blocks < kMaxI32) {
             const StripArgs sa{a, ylen, strips, ztiles, s};

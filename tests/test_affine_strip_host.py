@@ -4,7 +4,8 @@ grid it takes the kernel's bookkeeping -- the last image of a chunk against
 that of the one before, the band against the ring -- stays within the loads of
 a chunk and the ring, in 64-bit arithmetic as on the device.  Workgroups: the
 parts of the y range in order, each strip of a part once, an XCD's workgroups
-of a part on neighbouring strips.  Stores: whole lines streamed at any size."""
+of a part on neighbouring strips.  Stores: whole lines streamed at any size.
+Parts: the lengths measured fastest."""
 import os
 import subprocess
 
@@ -70,6 +71,13 @@ int main() {
             need((strip_stores(bytes, false, fits) == StripStores::kPhase) ==
                      (fits && bytes > 200000000), "other rows", bytes, fits);
         }
+    // short parts for outputs of whole lines that a part's band does not burden
+    need(strip_part(StripStores::kLines, 357000000, 0.26, 0.22) == 32 &&
+             strip_part(StripStores::kLines, 3600000000, 0.29, 0.24) == 64 &&
+             strip_part(StripStores::kLines, 178000000, 0.77, 0.63) == 64 &&
+             strip_part(StripStores::kPhase, 519000000, 0.65, 0.26) == 256 &&
+             strip_part(StripStores::kPlain, 82000000, 0.29, 0.24) == 256,
+         "part", 0.0, 0.0);
     for (int64_t strips : {1, 2, 7, 8, 9, 176, 1001, 4096})
         for (int64_t parts : {1, 2, 5}) {
             std::vector<int> seen(strips * parts, 0);
