@@ -11,6 +11,7 @@
 #include "common.hpp"
 #include "deskew.h"
 #include "kernels.hpp"
+#include "rows.hpp"
 
 using namespace dsk;
 
@@ -275,7 +276,6 @@ constexpr int64_t kFewTilesPerCU = 6;
 //  * without a volume, stacks of up to kSmallProjBytes do better unpaced, in
 //    us: 300x400x1024 uint16 (246 MB) 69.5 against 74.0, 128x512x2000 (262 MB)
 //    63.0 against 66.3; 256x512x1600 (419 MB) 111 against 106 paced
-constexpr int64_t kSmallProjBytes = 300000000;
 
 static dsk_tune default_tune(const void *in, int in_is_f32, dsk_dims d, int64_t in_plane,
                       const float *vol, int64_t width) {
@@ -324,19 +324,6 @@ static int check_forward(const void *in, dsk_dims d, const InLayout &lay, const 
 //     64x256x512 (3) 16.7 -> 12.7; 128x320x512 (5) 30.7 -> 32.1
 constexpr int64_t kSplitVolume = 10, kSplitVolumeAlone = 24, kSplitProjections = 12;
 
-// Projections of more tiles go to the row kernel (64 columns of 4 rows a
-// wavefront) where the tiles meet at most kFewPlanes planes, or where the rows
-// are short and the stack has up to kSmallProjBytes.  us, k_forward_vec in its
-// best shape -> row kernel:
-//   few planes: 50x1304x87 into 3653 uint16 (4.7) 25.5 -> 18.6, 40x512x512
-//     into 3846 (9) 15.7 -> 13.7, float32 15.2 -> 13.3
-//   uint16 rows: 401x1209x130 102 -> 60, 256x900x200 67 -> 44, 512x1024x256
-//     119 -> 105, 200x712x512 58.0 -> 54.8; 300x600x1024 97 -> 122
-//   float32 rows: 401x1209x130 86 -> 77, 256x900x200 52.8 -> 52.3;
-//     512x1024x256 146 -> 152, 300x900x300 79 -> 87
-constexpr int64_t kFewPlanes = 16;
-constexpr int32_t kShortRow16 = 512, kShortRow32 = 200;
-
 int launch_forward_default(const void *in, int in_is_f32, dsk_dims d, const InLayout &lay,
                            const double *offs, double shift, int64_t origin, float *vol,
                            float *psum, float *pmax, int64_t width, hipStream_t stream) {
@@ -348,13 +335,9 @@ int launch_forward_default(const void *in, int in_is_f32, dsk_dims d, const InLa
     const int64_t quarters = !vol ? kSplitProjections
                                   : (psum || pmax ? kSplitVolume : kSplitVolumeAlone);
     const bool split = 4 * tiles * d.rows <= quarters * device_cus();
-    // about how many planes a tile meets in a uniform scan: (C + 256) N / (W - C)
-    const bool few =
-        ((int64_t)d.cols + 256) * d.planes <= kFewPlanes * (width - d.cols) ||
-        (d.cols <= (in_is_f32 ? kShortRow32 : kShortRow16) &&
-         (int64_t)d.planes * d.rows * d.cols * (in_is_f32 ? 4 : 2) <= kSmallProjBytes);
     // (the row kernel's element and workgroup indexes are 32-bit)
-    const bool rows = !vol && few && lay.row < (int64_t(1) << 28) &&
+    const bool rows = !vol && by_rows(d.planes, d.rows, d.cols, width, in_is_f32 != 0) &&
+                      lay.row < (int64_t(1) << 28) &&
                       (width + 63) / 64 * (d.rows / kProjectRows + 1) <= kMaxI32;
     if ((split || rows) && width >= 4 &&
         vec_mode(kDefaultTune, d, width, in, in_is_f32, vol, lay.plane) != VEC_NONE &&
