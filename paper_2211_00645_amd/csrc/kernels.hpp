@@ -1061,9 +1061,8 @@ struct VecTile {
 // Edge columns of launches with a volume (the at most 3 unaligned columns
 // at each end of every row, present only when W is not a multiple of 4,
 // and then at least one per row): lane e handles slot e % 6 of row e / 6;
-// empty slots and rows past
-// the end repeat their row's first edge column (identical values to
-// identical addresses), so every lane stays active -- the per-plane
+// empty slots and rows past the end repeat their row's first edge column
+// (identical values to identical addresses), so every lane stays active -- the per-plane
 // coefficients are shared across lanes -- and every store is unconditional.
 // Two pixel loads per plane, issued UNR planes ahead of the stores.  Same
 // per-voxel arithmetic and plane order as every other path.  Few lanes
@@ -1081,7 +1080,7 @@ __device__ __forceinline__ void fwd_edge_lane(const FwdArgs<TIn> &a, int e) {
     if (x < 0) x = 0;   // unreachable when W % 4 != 0
     const int64_t rstep = a.in_plane, ostep = a.vol_plane;
     const TIn *rp = a.in + (int64_t)r * a.in_row;
-    float *op = a.vol ? a.vol + (int64_t)r * W + x : nullptr;
+    float *op = a.vol + (int64_t)r * W + x;
     CoefCache cc;
     cc.init(a.offs, a.shift, a.origin, a.N);
     double acc = 0.0;
@@ -1112,10 +1111,9 @@ __device__ __forceinline__ void fwd_edge_lane(const FwdArgs<TIn> &a, int e) {
                 const float d = fmaf(whi[u], hi[u], wlo[u] * lo[u]);
                 acc += (double)d;
                 mx = fmaxf(mx, d);
-                if (op)
-                    store_f32<NT>(bounded(op + (int64_t)(n0 + u) * ostep, 1, a.vol,
-                                          a.vol + (int64_t)a.N * a.vol_plane),
-                                  d);
+                store_f32<NT>(bounded(op + (int64_t)(n0 + u) * ostep, 1, a.vol,
+                                      a.vol + (int64_t)a.N * a.vol_plane),
+                              d);
             }
         }
 #pragma unroll
