@@ -27,6 +27,9 @@ SEED, BLOBS = 2, 2000
 HBM_PEAK_GBS = 8000.0
 METRIC = "deskewed voxels/s & HBM GB/s, 512×512×2048 u16 stack; p99 live-stack latency"
 KERNEL_SOURCES = ["paper_2211_00645_amd/csrc/kernels.hpp",
+                  "paper_2211_00645_amd/csrc/window.hpp",
+                  "paper_2211_00645_amd/csrc/quad.hpp",
+                  "paper_2211_00645_amd/csrc/xcd.hpp",
                   "paper_2211_00645_amd/csrc/deskew.hip",
                   "paper_2211_00645_amd/csrc/common.hpp"]
 PMC_SUMMARY = os.path.join(ROOT, "profiles", "forward_512x512x2048_pmc.md")

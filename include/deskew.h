@@ -164,7 +164,7 @@ int dsk_deskew_offsets_tuned(const void *in, int in_is_f32, dsk_dims d,
 /* Launch-shape tuner for one frame (the shape a live stream deskews over
  * and over).  Times candidate shapes -- one or two 4-column groups per
  * lane, unpaced and paced at 5000-6000 GB/s with a volume (9000-12000
- * without), and the default -- for `reps`
+ * without), and the default's vector shape -- for `reps`
  * rounds (3..64), a burst of 3 back-to-back launches of each shape per
  * round, round-robin after one untimed round, re-times the front runners
  * in longer back-to-back runs, on the caller's own buffers and stream, and
@@ -172,7 +172,9 @@ int dsk_deskew_offsets_tuned(const void *in, int in_is_f32, dsk_dims d,
  * 0.5% of the fastest, the one paced slowest; with a volume its pace then
  * steps down by at least 100 GB/s and to at most 5800, clear
  * of the pacing cliff (*ms, host, may be NULL: the mean time measured for
- * the returned shape).  Arguments as
+ * the returned shape).  A shape names the vector kernel: without one (tune
+ * NULL) frames of few tiles and projections of short rows go to kernels of
+ * their own, which are the faster there.  Arguments as
  * dsk_deskew_offsets_tuned.  Every trial computes the full result, so the
  * outputs may be written (with the correct values) or, when the choice is
  * already known, left untouched: call the forward with *tune afterwards.

@@ -147,7 +147,10 @@ def autotune(stack: torch.Tensor, angle_deg=None, step_um=None, pixel_um=None, *
     ``{"tune": shape dict, "ms": mean time}``; the choice is
     remembered per frame (and in the ``DSK_TUNE_CACHE`` file when that
     variable is set), so later calls return at once.  Pass the shape as
-    ``deskew(..., tune=...)``, or call ``deskew(..., tune="auto")``.
+    ``deskew(..., tune=...)``, or call ``deskew(..., tune="auto")``.  A shape
+    names the vector kernel: for frames of few tiles (64x128x256) and for
+    projections of short rows ``tune=None``, which picks other kernels there,
+    is the faster.
     """
     shape, shift, _, res = _setup(stack, angle_deg, step_um, pixel_um, offsets, origin, width,
                                   vol, psum, pmax, out)

@@ -2,7 +2,7 @@
 deskewed by ONE graph launch.
 
 The graph holds either one persistent kernel over all jobs or one plain
-paced launch per job (default shape, or each job frame's tuned shape).  The
+launch per job (default shape, or each job frame's tuned shape).  The
 library's autotuner times the persistent kernel's candidate shapes (threads
 per workgroup, columns per thread, plane unroll, pacing) and the per-job
 modes on the batch's own buffers, keeps the fastest, and caches the choice
@@ -145,9 +145,12 @@ class Batch:
 
 
 class JobLauncher:
-    """Launch per-call job lists with one persistent kernel (the serving
-    path): the job table is encoded into pinned host memory and copied to
-    the device on the launch stream, so nothing is allocated per launch.
+    """Launch per-call job lists (the serving path): one persistent kernel
+    over the jobs, except that without a ``tune`` a job with a volume that
+    moves 400 MB or more goes out in a launch of its own.  The job table is
+    encoded into pinned host memory; lists of up to 32 jobs in the default
+    shape travel in the launch's arguments, others are copied to the device
+    on the launch stream.  No device memory is allocated per launch.
     ``max_jobs`` bounds the table size; ``slots`` tables rotate so a table
     is not overwritten while an earlier copy may still be pending."""
 

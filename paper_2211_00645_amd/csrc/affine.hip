@@ -21,9 +21,10 @@
 // nothing else: 2.70 ms on the 512x512x2048 stack, 5.4 TB/s).  Measured:
 //   512x512x2048, 0.4 um, 15.6 GB: 3.24 ms, 4.81 TB/s (one wavefront per
 //     4-row strip with a float ring: 3.40; one row: 4.40; one-shot: 17.4)
-//   150x203x1001, 45 deg, 0.2 um, 0.85 GB: 0.205 ms, 4.1 TB/s (one-shot, the
-//     only kernel that took it: 1.345)
-//   200x301x777, 35 deg, 0.6 um, 1.66 GB: 0.364 ms, 4.6 TB/s
+//   150x203x1001, 45 deg, 0.2 um, 0.85 GB: 0.198 ms, 4.3 TB/s (one-shot, the
+//     only kernel that took it: 1.340)
+//   512x512x2048, dy 0.38 um (0.95 images a step), 5.5 GB: 1.13 ms, 4.85 TB/s
+//   200x301x777, 35 deg, 0.6 um, 1.66 GB, three outputs in turn: 0.475 ms
 #include <cmath>
 #include <cstdint>
 

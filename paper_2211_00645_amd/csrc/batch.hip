@@ -1,5 +1,5 @@
 // batch.hip -- ragged batches of uint16 stacks in one graph launch: either
-// one persistent kernel over all jobs (device job table) or one plain paced
+// one persistent kernel over all jobs (device job table) or one plain
 // launch per job, whichever the autotuner measures faster on the batch's own
 // buffers (on-disk cache of the choice), captured in a HIP graph.
 #include <hip/hip_runtime.h>

@@ -260,11 +260,17 @@ const char *tiling_name(const void *in, int in_is_f32, dsk_dims d, const float *
 //    74.3;
 //  * up to kSmallBytes moved and kSmallPlanes planes that cache absorbs most
 //    of the writes and the wavefronts cannot drift far apart, so a launch
-//    does better unpaced, in us over stacks in turn: 64x512x1024 uint16 (231
-//    MB) 42.4 against 45.4, 40x1000x800 (210 MB) 36.4 against 42.0;
-//    64x512x2048 (426 MB) 90.0 against 80.4 paced.  Unaligned 16-bit frames do
-//    better paced at any size (80x511x1023: 5286 GB/s against 4971), and more
-//    planes need the pacing (256x256x512: 4441 against 3809);
+//    does better unpaced while the stacks in use are few.  us unpaced / paced,
+//    over 3 stacks in turn (one stack again and again is the same) and over 8:
+//    64x512x1024 uint16 (225 MB) 36.5 / 42.4 and 43.4 / 44.1, 32x512x2048 (207
+//    MB) 36.1 / 40.2 and 47.1 / 43.7, 40x1000x800 (210 MB) 35.0 / 40.1 and 48.3 /
+//    42.8, 32x512x1024 (106 MB) 20.8 / 21.7 and 24.4 / 24.7.  Above, the pair
+//    turns with the method: 64x512x2048 (426 MB) over 4 stacks in turn 87.7 /
+//    78.7, which is how a live view's stacks come and what the default follows;
+//    one stack again and again 66.3 / 78.5, its buffers partly in the cache,
+//    which is what the tuner times.  Unaligned 16-bit frames do better paced at
+//    any size (80x511x1023: 59.3 / 53.6 and 60.2 / 58.1), and more planes need
+//    the pacing (256x256x512: 3809 GB/s unpaced, 4441 paced);
 //  * with few wavefronts a compute unit a 4-plane pipeline keeps enough
 //    loads in flight: 256x256x512 (5 wavefronts) 4409 -> 5140, 128x320x512
 //    (5) 45.4 -> 39.8 us; from 7 on the two are equal, from 14 on 2 planes

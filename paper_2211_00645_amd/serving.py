@@ -11,9 +11,10 @@ pipeline, with continuous batching:
   * a request is admitted when a launch slot (a stream) is free and its
     bytes (input + volume + projections) fit in the remaining budget;
     requests larger than the whole budget are rejected;
-  * all admitted requests waiting at that moment go out together in ONE
-    persistent launch over every channel of every request, so work that
-    arrives while other work is on the GPU joins as soon as a slot frees;
+  * all admitted requests waiting at that moment go out together as ONE job
+    list over every channel of every request (one persistent launch, and one
+    of its own for each large stack), so work that arrives while other work
+    is on the GPU joins as soon as a slot frees;
   * completion is an event after the projections' copy to host; it frees
     the slot and the request's bytes, which admits waiting requests.
 
@@ -355,9 +356,9 @@ class GPUExecutor:
     """Deskew + projections on the GPU.  Inputs come from a device-resident
     pool (``pool[(rows, cols, channel)]`` is a uint16 [max_planes][rows]
     [cols] tensor; a request uses its first ``planes`` planes), standing in
-    for camera frames already delivered to HBM.  Each submit is ONE
-    persistent launch over all channels of all requests in the batch on the
-    slot's stream, followed by the projections' copy to a pinned host
+    for camera frames already delivered to HBM.  Each submit is ONE job
+    list (:class:`batch.JobLauncher`) over all channels of all requests in the
+    batch on the slot's stream, followed by the projections' copy to a pinned host
     buffer of the batch and an event; each request's results are views of
     that buffer (it is freed, back to the pinned-memory cache, when they
     are).
