@@ -411,9 +411,9 @@ extern "C" int dsk_affine_u16(const uint16_t *in, dsk_dims d, dsk_geom g, double
         const int32_t ztiles = (d.cols + (phase ? 31 : 0) + kStripCols - 1) / kStripCols;
         const int64_t per_class = ((int64_t)d.rows + s - 1) / s;
         const int64_t strips = s * ((per_class + kStripRows - 1) / kStripRows) * ztiles;
-        const int64_t ylen = strip_ylen(strips, ny, strip_wg_per_cu(phase),
-                                        2 * (int64_t)d.planes * plane_px,
-                                        strip_part(stores, 4 * ny * plane_px, a.uy, a.uz));
+        const int64_t stack_bytes = 2 * (int64_t)d.planes * plane_px;
+        const int64_t ylen = strip_ylen(strips, ny, strip_wg_per_cu(phase), stack_bytes,
+                                        strip_part(stores, stack_bytes, a.uy, a.uz));
         const int64_t blocks = strips * ((ny + ylen - 1) / ylen);
         if (blocks < kMaxI32) {
             const StripArgs sa{a, ylen, strips, ztiles, s};

@@ -61,23 +61,26 @@ inline StripStores strip_stores(int64_t out_bytes, bool whole_lines, bool phase_
 // order, so short ones keep the planes written at a time together; each loads
 // its band of images anew.  us over three outputs in turn, 256 / 64 / 32 y
 // values, and the kernel before this one:
-//   whole lines, up to kShortPartBytes: 161x64x960 into 1451 (357 MB) 70.4 / 68.3
-//     / 57.9, before 67.2; 120x96x800 (328 MB) 67.1 / 64.2 / 55.9, 64.7;
-//     100x256x512 (400 MB) 82.5 / 81.9 / 68.5, 83.6; 70x512x448 (682 MB) 138.8 /
-//     136.6 / 137.4, 138.6
-//   larger: 256x512x1024 (3.6 GB) 782 / 784 / 878, 900; 64x128x1984 (2.2 GB)
-//     421 / 420 / 422, 424
+//   whole lines, stacks up to kShortPartStack: 161x64x960 (20 MB into 357) 70.4 /
+//     68.3 / 57.9, before 67.2; 120x96x800 (18 MB) 67.1 / 64.2 / 55.9, 64.7;
+//     100x256x512 (26 MB) 82.5 / 81.9 / 68.5, 83.6; 70x512x448 (32 MB) 138.8 / 136.6
+//     / 137.4, 138.6; 200x128x1024 (52 MB) 165 / 164 / 140, 172; 120x960x256 (59 MB
+//     into 897) 177 / 174 / 154, 166; 470x153x448 (64 MB) 152 / 144 / 141, 165
+//   larger: 127x832x384 (81 MB) 230 / 230 / 234, 276; 363x320x448 (104 MB) 300 / 319
+//     / 360, 425; 376x320x512 (123 MB) 192 / 204 / 245, 271; 100x512x1024 (105 MB)
+//     520 / 483 / 544, 573; 60x1024x1024 (126 MB) 855 / 796 / 865, 953; 256x512x1024
+//     (268 MB) 782 / 784 / 878, 900
 //   wide bands: 200x128x512 at 0.15 um (55 images) 37.5 / 32.6 / 38.8, 119
 //   runs at line boundaries (wider windows, 256 / 64): 200x301x777 479 / 514,
 //     150x203x1001 133 / 147
 //   plain stores: equal (200x64x333 22.9 / 23.7, 28x667x135 19.6 / 19.4)
-constexpr int64_t kShortPartBytes = 700000000;
+constexpr int64_t kShortPartStack = 70000000;
 constexpr double kShortPartBand = 24.0;
 
-inline int64_t strip_part(StripStores stores, int64_t out_bytes, double uy, double uz) {
+inline int64_t strip_part(StripStores stores, int64_t stack_bytes, double uy, double uz) {
     if (stores != StripStores::kLines) return 256;
     const double band = (strip_window(false) - 1) * fabs(uz) + kChunk * fabs(uy) + 3.0;
-    return out_bytes <= kShortPartBytes && band <= kShortPartBand ? 32 : 64;
+    return stack_bytes <= kShortPartStack && band <= kShortPartBand ? 32 : 64;
 }
 
 // Part of the y range and strip of workgroup b.  The parts go out one after

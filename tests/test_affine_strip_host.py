@@ -71,12 +71,13 @@ int main() {
             need((strip_stores(bytes, false, fits) == StripStores::kPhase) ==
                      (fits && bytes > 200000000), "other rows", bytes, fits);
         }
-    // short parts for outputs of whole lines that a part's band does not burden
-    need(strip_part(StripStores::kLines, 357000000, 0.26, 0.22) == 32 &&
-             strip_part(StripStores::kLines, 3600000000, 0.29, 0.24) == 64 &&
-             strip_part(StripStores::kLines, 178000000, 0.77, 0.63) == 64 &&
-             strip_part(StripStores::kPhase, 519000000, 0.65, 0.26) == 256 &&
-             strip_part(StripStores::kPlain, 82000000, 0.29, 0.24) == 256,
+    // short parts for whole lines of small stacks that a part's band does not burden
+    need(strip_part(StripStores::kLines, 20000000, 0.26, 0.22) == 32 &&
+             strip_part(StripStores::kLines, 59000000, 0.17, 0.14) == 32 &&
+             strip_part(StripStores::kLines, 104000000, 0.17, 0.14) == 64 &&
+             strip_part(StripStores::kLines, 26000000, 0.77, 0.63) == 64 &&
+             strip_part(StripStores::kPhase, 62000000, 0.65, 0.26) == 256 &&
+             strip_part(StripStores::kPlain, 8000000, 0.29, 0.24) == 256,
          "part", 0.0, 0.0);
     for (int64_t strips : {1, 2, 7, 8, 9, 176, 1001, 4096})
         for (int64_t parts : {1, 2, 5}) {
