@@ -12,6 +12,7 @@
 #include "deskew.h"
 #include "kernels.hpp"
 #include "rows.hpp"
+#include "split.hpp"
 
 using namespace dsk;
 
@@ -319,17 +320,6 @@ static int check_forward(const void *in, dsk_dims d, const InLayout &lay, const 
     return DSK_OK;
 }
 
-// Tiles per compute unit up to which a frame goes to the split kernel, in
-// quarters.  us, k_forward_vec in its best shape -> split:
-//   volume and projections: 64x128x256 uint16 (1 tile) 14.8 -> 10.2,
-//     302x64x128 (1.25) 69 -> 42, 128x128x512 (2) 30.7 -> 21.4; 40x400x500
-//     (4.7) 14.8 -> 18.1, 256x256x512 (5) 76 -> 103
-//   volume alone (no sums, so no LDS and no barriers): 37x131x517 (1.5)
-//     11.2 -> 9.5, 128x256x512 (4) 35.6 -> 26.6; 200x512x512 (8) 89 -> 142
-//   projections alone: 64x128x256 15.8 -> 8.7, 302x64x128 28 -> 19,
-//     64x256x512 (3) 16.7 -> 12.7; 128x320x512 (5) 30.7 -> 32.1
-constexpr int64_t kSplitVolume = 10, kSplitVolumeAlone = 24, kSplitProjections = 12;
-
 int launch_forward_default(const void *in, int in_is_f32, dsk_dims d, const InLayout &lay,
                            const double *offs, double shift, int64_t origin, float *vol,
                            float *psum, float *pmax, int64_t width, hipStream_t stream) {
@@ -338,9 +328,8 @@ int launch_forward_default(const void *in, int in_is_f32, dsk_dims d, const InLa
     // the split kernel's tile is the general vector tile: 64 groups
     const int64_t tiles = (width + 255) / 256;
     const uintptr_t im = in_is_f32 ? 3 : 1;
-    const int64_t quarters = !vol ? kSplitProjections
-                                  : (psum || pmax ? kSplitVolume : kSplitVolumeAlone);
-    const bool split = 4 * tiles * d.rows <= quarters * device_cus();
+    const bool split = by_split(d.planes, d.rows, d.cols, width, vol != nullptr, psum || pmax,
+                                device_cus());
     // (the row kernel's element and workgroup indexes are 32-bit)
     const bool rows = !vol && by_rows(d.planes, d.rows, d.cols, width, in_is_f32 != 0) &&
                       lay.row < (int64_t(1) << 28) &&
