@@ -329,7 +329,11 @@ extern "C" int dsk_deskew_autotune(const void *in, int in_is_f32, dsk_dims d,
     // a stream under capture cannot be timed: there the shape that another
     // tiling of the frame was given serves
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();   // not the next launch's error
+        cap = hipStreamCaptureStatusNone;
+    }
+    if (cap != hipStreamCaptureStatusNone)
         for (const char *tiling : {"lines", "aligned", "general", "scalar"})
             if (remembered(key_of(tiling))) return DSK_OK;
     dsk_tune best{};
